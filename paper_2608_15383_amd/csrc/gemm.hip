@@ -106,8 +106,11 @@ __device__ __forceinline__ void wait_loads() {
 }
 
 // Workgroup barrier that orders LDS accesses but does not wait for loads.
+// The barrier instruction itself waits for nothing: a wavefront's last LDS
+// writes are only in LDS once its LDS counter is at zero.
 __device__ __forceinline__ void barrier() {
   asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));  // lgkmcnt(0) only
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }

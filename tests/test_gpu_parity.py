@@ -535,6 +535,19 @@ def test_prefill_full_size_whole_expert_and_every_row(olmoe):
     experts.cache.clear()
 
 
+def test_prefill_repeats_bit_for_bit(olmoe):
+    """100 prefill calls on one input give the same bits: the epilogues hand
+    their output tile between wavefronts through LDS, and a wavefront that
+    reads before another's last write has landed changes 16 columns of a row."""
+    lay, layer, _ = olmoe
+    h = dev(lay.h)
+    y0, y = torch.empty_like(h), torch.empty_like(h)
+    api.moe_forward(layer.cache, h, layer.wr, y0, layer.ws, path=MFMA)
+    for i in range(100):
+        api.moe_forward(layer.cache, h, layer.wr, y, layer.ws, path=MFMA)
+        assert torch.equal(y, y0), i
+
+
 def test_prefill_paths_agree(olmoe):
     lay, layer, experts = olmoe
     sub = _sub(lay, 256)
