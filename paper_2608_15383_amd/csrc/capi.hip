@@ -450,7 +450,9 @@ int32_t emoe_route(const emoe_dims* dims, int32_t T, const uint16_t* h, const ui
     EMOE_LAUNCH(EMOE_K_ROUTER, stream,
                 launch_router_logits(T, E, dims->d_model, h, w_router, logits, stream));
   if (T > 0)
-    EMOE_LAUNCH(EMOE_K_TOPK, stream, launch_topk(T, E, k, renormalize, z, topk_ids, topk_w, stream));
+    EMOE_LAUNCH(EMOE_K_TOPK, stream,
+              launch_topk(T, E, k, renormalize, LogitSource{z, nullptr, nullptr, 0}, topk_ids, topk_w,
+                          stream));
   EMOE_LAUNCH(EMOE_K_GROUP, stream,
               launch_group(T * k, E, topk_ids, counts, offsets, sorted_pairs, active, n_active,
                            nullptr, nullptr, 1, stream));
@@ -838,28 +840,54 @@ int32_t forward_impl(emoe_cache* c, int32_t T, const uint16_t* h, const uint16_t
 
   // Route (Eq. 1) and group by expert.  On the MFMA path the router also sums
   // each token row's input groups (the accumulator starts of the gate/up MFMA
-  // chains) when d is a multiple of 512; otherwise a separate pass forms them
-  // below.
-  const float* z = logits_override ? logits_override : logits;
+  // chains) when d is a multiple of 512; otherwise extra workgroups of the
+  // top-k launch form them (a launch of their own took 2 to 5 us).  A small call's router leaves the logits as sums
+  // over slices of d, in the pair-output array, which only the down projection
+  // writes (k * d floats per token hold E doubles per slice: a slice is at
+  // least 512 inputs, and E at most 256).
   float* tok_bias = reinterpret_cast<float*>(ws + L.tok_bias);
   const bool uses_mfma = path != EMOE_PATH_GEMV;
   const bool fused_bias = uses_mfma && !logits_override && d % 512 == 0;
+  LogitSource src{logits_override ? logits_override : logits, nullptr, logits, 0};
   if (!logits_override) {
+    const int slices = router_slices(T, E, d);
+    double* parts = slices > 1 ? reinterpret_cast<double*>(pair_out) : nullptr;
     EMOE_LAUNCH(EMOE_K_ROUTER, stream,
                 launch_router_logits(T, E, d, h, w_router, logits, stream,
-                                     fused_bias ? tok_bias : nullptr));
+                                     fused_bias ? tok_bias : nullptr, parts, slices));
     ds.kernel_launches += 1;
+    if (parts) {
+      src.parts = parts;
+      src.slices = slices;
+    }
   }
-  if (P > kGroupWideMinPairs) {
+  RowBias rb;
+  if (uses_mfma && !fused_bias) {
+    rb.x = h;
+    rb.bias = tok_bias;
+    rb.d = d;
+  }
+  if (rb.x && path == EMOE_PATH_MIXED) {
+    // The mixed path (asked for by name) reports them as a kernel of their own.
+    EMOE_LAUNCH(EMOE_K_ROW_BIAS, stream, launch_row_bias(T, rb, stream));
+    ds.kernel_launches += 1;
+    rb = RowBias();
+  }
+  if (T <= kTopkGroupMaxTokens && P <= kGroupWideMinPairs && path != EMOE_PATH_MIXED) {
+    EMOE_LAUNCH(EMOE_K_TOPK, stream,
+                launch_topk_group(T, E, k, renormalize, src, ids, wts, counts, offsets, sorted,
+                                  active, n_active, tiles, pair_pos, mfma_rows, stream, rb));
+    ds.kernel_launches += 1;
+  } else if (P > kGroupWideMinPairs) {
     // Wide grouping: per-chunk counts (with the top-k when top_k divides 64),
     // then the placement.
     int32_t* chunk_counts = reinterpret_cast<int32_t*>(ws + L.chunk_counts);
     if (topk_count_fits(k)) {
       EMOE_LAUNCH(EMOE_K_TOPK, stream,
-                  launch_topk_count(T, E, k, renormalize, z, ids, wts, chunk_counts, stream));
+                  launch_topk_count(T, E, k, renormalize, src, ids, wts, chunk_counts, stream, rb));
       ds.kernel_launches += 1;
     } else {
-      EMOE_LAUNCH(EMOE_K_TOPK, stream, launch_topk(T, E, k, renormalize, z, ids, wts, stream));
+      EMOE_LAUNCH(EMOE_K_TOPK, stream, launch_topk(T, E, k, renormalize, src, ids, wts, stream, rb));
       EMOE_LAUNCH(EMOE_K_GROUP_COUNT, stream, launch_group_count(P, E, ids, chunk_counts, stream));
       ds.kernel_launches += 2;
     }
@@ -868,18 +896,13 @@ int32_t forward_impl(emoe_cache* c, int32_t T, const uint16_t* h, const uint16_t
                                    n_active, tiles, pair_pos, mfma_rows, stream));
     ds.kernel_launches += 1;
   } else {
-    EMOE_LAUNCH(EMOE_K_TOPK, stream, launch_topk(T, E, k, renormalize, z, ids, wts, stream));
+    EMOE_LAUNCH(EMOE_K_TOPK, stream, launch_topk(T, E, k, renormalize, src, ids, wts, stream, rb));
     EMOE_LAUNCH(EMOE_K_GROUP, stream,
                 launch_group(P, E, ids, counts, offsets, sorted, active, n_active, tiles, pair_pos,
                              mfma_rows, stream));
     ds.kernel_launches += 2;
   }
   const GroupView gv{sorted, offsets, active, n_active, tiles, mfma_rows};
-  if (uses_mfma && !fused_bias) {
-    // Accumulator start of the gate/up MFMA chains, once per call.
-    EMOE_LAUNCH(EMOE_K_ROW_BIAS, stream, launch_row_bias(T, d, h, tok_bias, stream));
-    ds.kernel_launches += 1;
-  }
 
   // One wave's projections: the GEMV kernels for the experts below mfma_rows
   // rows, the MFMA kernels for the others (on the mixed path both, gate/up

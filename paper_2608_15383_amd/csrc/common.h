@@ -267,14 +267,51 @@ hipError_t launch_quantize(int d, int f, int n_experts, const uint16_t* w_gate,
                            const uint16_t* w_up, const uint16_t* w_down, uint8_t* records,
                            int32_t* range_flag, hipStream_t stream);
 
+// Where the top-k takes a call's logits from: fp32 `logits` (slices == 0), or
+// the router's fp64 sums parts[slice][t][e] over `slices` slices of d, which
+// the top-k adds and also stores, rounded, as logits_out.
+constexpr int kRouterMaxSlices = 8;
+struct LogitSource {
+  const float* logits;
+  const double* parts;
+  float* logits_out;
+  int32_t slices;
+};
+
+// Row sums riding along with a top-k launch (x null: none): bias[t][g] = -136
+// * the sum of the 128-input group g of row t of x [tokens][d], fp32.
+struct RowBias {
+  const uint16_t* x = nullptr;
+  float* bias = nullptr;
+  int32_t d = 0;
+};
+
+// Slices of d over which launch_router_logits should split a call (1: none).
+int router_slices(int tokens, int n_experts, int d);
+
 // tok_bias (optional, d a multiple of 512): also -136 * the sum of each
-// 128-input group of every token row, fp32 [tokens][d/128].
+// 128-input group of every token row, fp32 [tokens][d/128].  With parts, the
+// logits' fp64 sums over each of `slices` slices go there instead of logits.
 hipError_t launch_router_logits(int tokens, int n_experts, int d, const uint16_t* h,
                                 const uint16_t* w_router, float* logits, hipStream_t stream,
-                                float* tok_bias = nullptr);
+                                float* tok_bias = nullptr, double* parts = nullptr, int slices = 1);
 
-hipError_t launch_topk(int tokens, int n_experts, int top_k, int renormalize, const float* logits,
-                       int32_t* topk_ids, float* topk_w, hipStream_t stream);
+hipError_t launch_topk(int tokens, int n_experts, int top_k, int renormalize,
+                       const LogitSource& src, int32_t* topk_ids, float* topk_w, hipStream_t stream,
+                       const RowBias& rb = RowBias());
+
+// The row sums as a launch of their own.
+hipError_t launch_row_bias(int tokens, const RowBias& rb, hipStream_t stream);
+
+// launch_topk and launch_group in one launch, for calls of at most
+// kTopkGroupMaxTokens tokens.
+constexpr int kTopkGroupMaxTokens = 64;
+hipError_t launch_topk_group(int tokens, int n_experts, int top_k, int renormalize,
+                             const LogitSource& src, int32_t* topk_ids, float* topk_w,
+                             int32_t* counts, int32_t* offsets, int32_t* sorted_pairs,
+                             int32_t* active, int32_t* n_active, int32_t* tile_offsets,
+                             int32_t* pair_pos, int mfma_rows, hipStream_t stream,
+                             const RowBias& rb = RowBias());
 
 // Grouping by expert (Sec. 3.4 step 1) in one workgroup; pair_pos receives
 // the inverse permutation (grouped position of each pair id), tile_offsets
@@ -293,8 +330,9 @@ hipError_t launch_group_count(int pairs, int n_experts, const int32_t* topk_ids,
 // one launch; only for top_k dividing 64 with 64 / top_k <= 16.
 constexpr bool topk_count_fits(int top_k) { return top_k >= 4 && 64 % top_k == 0; }
 hipError_t launch_topk_count(int tokens, int n_experts, int top_k, int renormalize,
-                             const float* logits, int32_t* topk_ids, float* topk_w,
-                             int32_t* chunk_counts, hipStream_t stream);
+                             const LogitSource& src, int32_t* topk_ids, float* topk_w,
+                             int32_t* chunk_counts, hipStream_t stream,
+                             const RowBias& rb = RowBias());
 hipError_t launch_group_place(int pairs, int n_experts, const int32_t* topk_ids,
                               const int32_t* chunk_counts, int32_t* counts, int32_t* offsets,
                               int32_t* sorted_pairs, int32_t* active, int32_t* n_active,
@@ -322,11 +360,9 @@ hipError_t launch_down_gemv(int d, int f, int top_k, int pairs, int n_experts,
 
 // Grouped MFMA projections.  h_bias / act_bias: -136 * the sum of each
 // 128-input group of the projection's input rows: h_bias per token, fp32
-// [tokens][d/128] (from the router, or launch_row_bias); act_bias by grouped
+// [tokens][d/128] (from the router or the top-k launch); act_bias by grouped
 // position, fp32 [f/128][pairs], written by the gate/up launch for the down
 // launch.  Each workgroup gathers its row tile's values once.
-hipError_t launch_row_bias(int tokens, int K, const uint16_t* x, float* bias, hipStream_t stream);
-
 hipError_t launch_gateup_mfma(int tokens, int d, int f, int top_k, int n_experts, const uint16_t* h,
                               const float* h_bias, const GroupView& gv, const WaveArg& wave,
                               const uint8_t* slot_bank, int64_t record_bytes, uint16_t* act,

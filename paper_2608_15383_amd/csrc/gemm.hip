@@ -517,35 +517,6 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
   }
 }
 
-// bias[t][g] = -136 * sum of x[t][128g .. 128g+127] (fp32, fixed order): the
-// accumulator start of the gate/up MFMA chains of every pair of token t.
-__global__ __launch_bounds__(256) void row_bias_kernel(int tokens, int K, const uint16_t* __restrict__ x,
-                                                       float* __restrict__ bias) {
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= tokens) return;
-  const int lane = lane_id();
-  const uint16_t* xr = x + (int64_t)t * K;
-  for (int c0 = 0; c0 < K / 8; c0 += 64) {
-    const int c = c0 + lane;
-    float s = 0.f;
-    if (c < K / 8) {
-      const uint4 v = *reinterpret_cast<const uint4*>(xr + 8 * c);
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        s += bf16_bits_to_f32(w[q] & 0xffffu);
-        s += bf16_bits_to_f32(w[q] >> 16);
-      }
-    }
-    // Sum over the 16 lanes holding one group.
-    s += __shfl_xor(s, 1);
-    s += __shfl_xor(s, 2);
-    s += __shfl_xor(s, 4);
-    s += __shfl_xor(s, 8);
-    if ((lane & 15) == 0 && c < K / 8) bias[(int64_t)t * (K / kGroup) + c / kChunks] = -kCodeBias * s;
-  }
-}
-
 inline int max_row_tiles(int pairs, int n_experts) {
   const int e = pairs < n_experts ? pairs : n_experts;
   return (pairs + kRows - 1) / kRows + e;
@@ -586,12 +557,6 @@ inline int mfma_grid(int n_ctiles, int pairs, int n_experts, int limit) {
 }
 
 }  // namespace
-
-hipError_t launch_row_bias(int tokens, int K, const uint16_t* x, float* bias, hipStream_t stream) {
-  if (tokens == 0) return hipSuccess;
-  launch(row_bias_kernel, dim3((tokens + 3) / 4), dim3(256), stream, tokens, K, x, bias);
-  return hipGetLastError();
-}
 
 hipError_t launch_gateup_mfma(int tokens, int d, int f, int top_k, int n_experts, const uint16_t* h,
                               const float* h_bias, const GroupView& gv, const WaveArg& wave,

@@ -3,7 +3,8 @@
 // lives in device_route.h.
 //
 //   router_logits_kernel: z[t][e] = fp32(sum_i h[t][i] * W_r[e][i]), fp64 sum
-//                         on fp64 MFMA.
+//                         on fp64 MFMA; a small call leaves fp64 sums over
+//                         slices of d, which its top-k adds and rounds.
 //   topk_kernel:          k largest logits per token (ties -> lower expert id)
 //                         and their softmax mixture weights in fp64.
 //   topk_count_kernel:    the same for the 64 / k tokens of one 64-pair chunk
@@ -25,10 +26,17 @@ typedef double f64x4_t __attribute__((ext_vector_type(4)));
 // take the same input for the same lane, so every product h_k * w_k is
 // formed once and exactly, and summed in fp64.  The four partial sums are
 // added in wavefront order and rounded once to fp32.
+// With parts (gridDim.z = S slices of d) the workgroup covers slice
+// blockIdx.z only and stores its fp64 sum to parts[slice][t][e] instead; the
+// top-k adds the slices in order and rounds.  A tile is 512 MFMAs of 64
+// cycles in a dependent chain per SIMD at d = 2048, so the few tiles of a
+// small call are bound by that chain and by the load rounds between, on as
+// few CUs: 16 tokens took 10.6 us on 4 workgroups.
 __global__ __launch_bounds__(256) void router_logits_kernel(int tokens, int n_experts, int d,
                                                             const uint16_t* __restrict__ h,
                                                             const uint16_t* __restrict__ wr,
                                                             float* __restrict__ logits,
+                                                            double* __restrict__ parts,
                                                             float* __restrict__ tok_bias) {
   __shared__ double part[4][4][64];
   const int lane = lane_id();
@@ -38,15 +46,16 @@ __global__ __launch_bounds__(256) void router_logits_kernel(int tokens, int n_ex
   // Rows past the end repeat the last row; their results are not stored.
   const int t = min(t0 + row, tokens - 1);
   const int e = min(e0 + row, n_experts - 1);
-  const int kq = d / 4;
-  const uint16_t* hp = h + (int64_t)t * d + wave * kq + 8 * q;
-  const uint16_t* wp = wr + (int64_t)e * d + wave * kq + 8 * q;
+  const int kq = d / (4 * (int)gridDim.z);
+  const int k0 = ((int)blockIdx.z * 4 + wave) * kq;
+  const uint16_t* hp = h + (int64_t)t * d + k0 + 8 * q;
+  const uint16_t* wp = wr + (int64_t)e * d + k0 + 8 * q;
   f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
   // Loads run kAhead steps of 32 inputs ahead of the MFMAs.
   constexpr int kAhead = 4;
   const int n = kq / 32;
-  // With tok_bias (d a multiple of 512, so every iteration of the loop below
-  // is one 128-input group), the first expert tile's workgroups also sum each
+  // With tok_bias (d a multiple of 512 per slice, so every iteration of the
+  // loop below is one 128-input group), the first expert tile's workgroups also sum each
   // group of their token rows.
   const bool sums = tok_bias != nullptr && blockIdx.y == 0;
   uint4 hb[kAhead], wb[kAhead];
@@ -81,7 +90,7 @@ __global__ __launch_bounds__(256) void router_logits_kernel(int tokens, int n_ex
       // The lane's 32 inputs of the group, then the four lanes of the row.
       gsum += __shfl_xor(gsum, 16);
       gsum += __shfl_xor(gsum, 32);
-      const int g = (wave * kq + 32 * i) / kGroup;
+      const int g = (k0 + 32 * i) / kGroup;
       if (q == 0 && t0 + row < tokens) tok_bias[(int64_t)(t0 + row) * (d / kGroup) + g] = -136.f * gsum;
     }
   }
@@ -95,21 +104,98 @@ __global__ __launch_bounds__(256) void router_logits_kernel(int tokens, int n_ex
     for (int r = 0; r < 4; ++r) {
       const double z = ((part[0][r][lane] + part[1][r][lane]) + part[2][r][lane]) + part[3][r][lane];
       const int tt = t0 + q + 4 * r, ee = e0 + row;
-      if (tt < tokens && ee < n_experts) logits[(int64_t)tt * n_experts + ee] = (float)z;
+      if (tt >= tokens || ee >= n_experts) continue;
+      if (parts)
+        parts[((int64_t)blockIdx.z * tokens + tt) * n_experts + ee] = z;
+      else
+        logits[(int64_t)tt * n_experts + ee] = (float)z;
     }
   }
 }
 
+// Selection from token t's logits: as given, or (src.slices > 0) the router's
+// slice sums added in order and rounded to fp32, which are then also stored
+// as the call's logits.
+__device__ __forceinline__ void topk_select_from(const LogitSource& src, int t, int tokens,
+                                                 int n_experts, int top_k, TopkState& st,
+                                                 uint64_t* scratch) {
+  if (src.slices == 0) {
+    wave_topk_select<false>(src.logits + (int64_t)t * n_experts, n_experts, top_k, st, scratch);
+    return;
+  }
+  const int lane = lane_id();
+#pragma unroll
+  for (int c = 0; c < kPerLane; ++c) {
+    const int e = lane + 64 * c;
+    st.v[c] = 0.f;
+    if (e >= n_experts) continue;
+    const double* p = src.parts + (int64_t)t * n_experts + e;
+    double v[kRouterMaxSlices];
+#pragma unroll
+    for (int s = 0; s < kRouterMaxSlices; ++s)
+      v[s] = s < src.slices ? p[(int64_t)s * tokens * n_experts] : 0.0;
+    double z = v[0];
+#pragma unroll
+    for (int s = 1; s < kRouterMaxSlices; ++s) z += v[s];
+    st.v[c] = (float)z;
+    src.logits_out[(int64_t)t * n_experts + e] = st.v[c];
+  }
+  wave_topk_select_loaded(n_experts, top_k, st, scratch);
+}
+
+// bias[t][g] = -136 * sum of x[t][128g .. 128g+127] (fp32, fixed order) of one
+// token row by one wavefront: the accumulator start of the gate/up MFMA
+// chains of every pair of token t.
+__device__ __forceinline__ void wave_row_bias(int t, int K, const uint16_t* __restrict__ x,
+                                              float* __restrict__ bias) {
+  const int lane = lane_id();
+  const uint16_t* xr = x + (int64_t)t * K;
+  for (int c0 = 0; c0 < K / 8; c0 += 64) {
+    const int c = c0 + lane;
+    float s = 0.f;
+    if (c < K / 8) {
+      const uint4 v = *reinterpret_cast<const uint4*>(xr + 8 * c);
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        s += bf16_to_f32(w[q] & 0xffffu);
+        s += bf16_to_f32(w[q] >> 16);
+      }
+    }
+    // Sum over the 16 lanes holding one group.
+    s += __shfl_xor(s, 1);
+    s += __shfl_xor(s, 2);
+    s += __shfl_xor(s, 4);
+    s += __shfl_xor(s, 8);
+    if ((lane & 15) == 0 && c < K / 8) bias[(int64_t)t * (K / kGroup) + c / (kGroup / 8)] = -136.f * s;
+  }
+}
+
+// Workgroups from `first` on form the row biases, one token per wavefront:
+// they ride along with the top-k launch, which saves one of their own.
+__device__ __forceinline__ bool row_bias_block(const RowBias& rb, int first, int tokens) {
+  if ((int)blockIdx.x < first) return false;
+  const int t = ((int)blockIdx.x - first) * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  if (t < tokens) wave_row_bias(t, rb.d, rb.x, rb.bias);
+  return true;
+}
+
+__global__ __launch_bounds__(256) void row_bias_kernel(int tokens, RowBias rb) {
+  row_bias_block(rb, 0, tokens);
+}
+
 __global__ __launch_bounds__(256) void topk_kernel(int tokens, int n_experts, int top_k,
-                                                   int renormalize, const float* __restrict__ logits,
+                                                   int renormalize, LogitSource src,
                                                    int32_t* __restrict__ topk_ids,
-                                                   float* __restrict__ topk_w) {
+                                                   float* __restrict__ topk_w, RowBias rb) {
   __shared__ uint64_t s_rank[4][64];  // per-wavefront top-k scratch
+  if (row_bias_block(rb, (tokens + 3) / 4, tokens)) return;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= tokens) return;
-  wave_topk<false>(logits + (int64_t)t * n_experts, n_experts, top_k, renormalize,
-                   topk_ids + (int64_t)t * top_k, topk_w + (int64_t)t * top_k,
-                   s_rank[threadIdx.x >> 6]);
+  TopkState st;
+  topk_select_from(src, t, tokens, n_experts, top_k, st, s_rank[threadIdx.x >> 6]);
+  wave_topk_store_ids<false>(st, top_k, topk_ids + (int64_t)t * top_k);
+  wave_topk_weights<false>(st, n_experts, top_k, renormalize, topk_w + (int64_t)t * top_k);
 }
 
 // Top-k of 64 / top_k tokens per workgroup, one wavefront each, when top_k
@@ -118,22 +204,24 @@ __global__ __launch_bounds__(256) void topk_kernel(int tokens, int n_experts, in
 // writes that chunk's per-expert counts (chunk_count_kernel's row), which
 // saves that launch.  Ids and weights as topk_kernel writes them.
 __global__ __launch_bounds__(1024) void topk_count_kernel(int tokens, int n_experts, int top_k,
-                                                          int renormalize,
-                                                          const float* __restrict__ logits,
+                                                          int renormalize, LogitSource src,
                                                           int32_t* __restrict__ topk_ids,
                                                           float* __restrict__ topk_w,
-                                                          int32_t* __restrict__ chunk_counts) {
+                                                          int32_t* __restrict__ chunk_counts,
+                                                          RowBias rb) {
   __shared__ uint64_t s_rank[16][64];  // per-wavefront top-k scratch
   __shared__ int s_pair[64];           // the chunk's expert ids, pair order
   __shared__ int row[EMOE_MAX_EXPERTS];
+  const int per = 64 / top_k;
+  if (row_bias_block(rb, (tokens + per - 1) / per, tokens)) return;
   const int lane = lane_id();
   const int wave = threadIdx.x >> 6;
   const int c = blockIdx.x;
-  const int t = c * (64 / top_k) + wave;
+  const int t = c * per + wave;
   for (int e = threadIdx.x; e < n_experts; e += blockDim.x) row[e] = 0;
   if (t < tokens) {
     TopkState st;
-    wave_topk_select<false>(logits + (int64_t)t * n_experts, n_experts, top_k, st, s_rank[wave]);
+    topk_select_from(src, t, tokens, n_experts, top_k, st, s_rank[wave]);
     wave_topk_store_ids<false>(st, top_k, topk_ids + (int64_t)t * top_k);
 #pragma unroll
     for (int r = 0; r < kPerLane; ++r)
@@ -163,6 +251,33 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(
   __shared__ GroupShared<kGroupThreads> sh;
   block_group<kGroupThreads, false>(sh, pairs, n_experts, ids, counts, offsets, sorted_pairs,
                                     active, n_active, tile_offsets, pair_pos, mfma_rows);
+}
+
+// Top-k and grouping of a small call in one launch: workgroup 0's 16
+// wavefronts take the tokens in turn, then group all pairs.  Bound by latency:
+// each token costs its wavefront about 0.7 us, so kTopkGroupMaxTokens
+// sends few tokens per wavefront here; the separate launches cost
+// their start, their gap and a round trip of the ids.
+__global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(
+    int tokens, int n_experts, int top_k, int renormalize, LogitSource src,
+    int32_t* __restrict__ topk_ids, float* __restrict__ topk_w, int32_t* __restrict__ counts,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ sorted_pairs, int32_t* __restrict__ active,
+    int32_t* __restrict__ n_active, int32_t* __restrict__ tile_offsets,
+    int32_t* __restrict__ pair_pos, int mfma_rows, RowBias rb) {
+  __shared__ uint64_t s_rank[kGroupThreads / 64][64];
+  __shared__ GroupShared<kGroupThreads> sh;
+  if (row_bias_block(rb, 1, tokens)) return;
+  const int wave = threadIdx.x >> 6;
+  for (int t = wave; t < tokens; t += kGroupThreads / 64) {
+    TopkState st;
+    topk_select_from(src, t, tokens, n_experts, top_k, st, s_rank[wave]);
+    wave_topk_store_ids<false>(st, top_k, topk_ids + (int64_t)t * top_k);
+    wave_topk_weights<false>(st, n_experts, top_k, renormalize, topk_w + (int64_t)t * top_k);
+  }
+  __threadfence_block();
+  __syncthreads();
+  block_group<kGroupThreads, false>(sh, tokens * top_k, n_experts, topk_ids, counts, offsets,
+                                    sorted_pairs, active, n_active, tile_offsets, pair_pos, mfma_rows);
 }
 
 // Grouping spread over many workgroups (large calls): 64-pair chunks, one per
@@ -323,33 +438,70 @@ hipError_t launch_group_place(int pairs, int n_experts, const int32_t* topk_ids,
   return hipGetLastError();
 }
 
+int router_slices(int tokens, int n_experts, int d) {
+  // Slices only while the tiles leave CUs without work (two workgroups per CU
+  // fill the matrix cores), and of whole 512-input quarters, so that every
+  // wavefront keeps whole 128-input groups.
+  const int tiles = ((tokens + 15) / 16) * ((n_experts + 15) / 16);
+  int s = 1;
+  while (2 * s <= kRouterMaxSlices && d % (512 * 2 * s) == 0 && tiles * 2 * s <= 512) s *= 2;
+  return s;
+}
+
 hipError_t launch_router_logits(int tokens, int n_experts, int d, const uint16_t* h,
                                 const uint16_t* w_router, float* logits, hipStream_t stream,
-                                float* tok_bias) {
+                                float* tok_bias, double* parts, int slices) {
   if (tokens == 0) return hipSuccess;
   if (d % 512 != 0) tok_bias = nullptr;
-  dim3 grid((tokens + 15) / 16, (n_experts + 15) / 16);
+  dim3 grid((tokens + 15) / 16, (n_experts + 15) / 16, parts ? slices : 1);
   launch(router_logits_kernel, grid, dim3(256), stream, tokens, n_experts, d, h, w_router, logits,
-         tok_bias);
+         parts, tok_bias);
   return hipGetLastError();
 }
 
-hipError_t launch_topk(int tokens, int n_experts, int top_k, int renormalize, const float* logits,
-                       int32_t* topk_ids, float* topk_w, hipStream_t stream) {
+namespace {
+inline int bias_blocks(const RowBias& rb, int tokens, int waves) {
+  return rb.x ? (tokens + waves - 1) / waves : 0;
+}
+}  // namespace
+
+hipError_t launch_row_bias(int tokens, const RowBias& rb, hipStream_t stream) {
   if (tokens == 0) return hipSuccess;
-  launch(topk_kernel, dim3((tokens + 3) / 4), dim3(256), stream, tokens, n_experts, top_k,
-         renormalize, logits, topk_ids, topk_w);
+  launch(row_bias_kernel, dim3(bias_blocks(rb, tokens, 4)), dim3(256), stream, tokens, rb);
+  return hipGetLastError();
+}
+
+hipError_t launch_topk(int tokens, int n_experts, int top_k, int renormalize,
+                       const LogitSource& src, int32_t* topk_ids, float* topk_w, hipStream_t stream,
+                       const RowBias& rb) {
+  if (tokens == 0) return hipSuccess;
+  launch(topk_kernel, dim3((tokens + 3) / 4 + bias_blocks(rb, tokens, 4)), dim3(256), stream, tokens,
+         n_experts, top_k, renormalize, src, topk_ids, topk_w, rb);
   return hipGetLastError();
 }
 
 hipError_t launch_topk_count(int tokens, int n_experts, int top_k, int renormalize,
-                             const float* logits, int32_t* topk_ids, float* topk_w,
-                             int32_t* chunk_counts, hipStream_t stream) {
+                             const LogitSource& src, int32_t* topk_ids, float* topk_w,
+                             int32_t* chunk_counts, hipStream_t stream, const RowBias& rb) {
   if (tokens == 0) return hipSuccess;
   if (top_k < 1 || 64 % top_k != 0 || 64 / top_k > 16) return hipErrorInvalidValue;
   const int per = 64 / top_k;  // tokens (wavefronts) per chunk
-  launch(topk_count_kernel, dim3((tokens + per - 1) / per), dim3(64 * per), stream, tokens,
-         n_experts, top_k, renormalize, logits, topk_ids, topk_w, chunk_counts);
+  launch(topk_count_kernel, dim3((tokens + per - 1) / per + bias_blocks(rb, tokens, per)),
+         dim3(64 * per), stream, tokens, n_experts, top_k, renormalize, src, topk_ids, topk_w,
+         chunk_counts, rb);
+  return hipGetLastError();
+}
+
+hipError_t launch_topk_group(int tokens, int n_experts, int top_k, int renormalize,
+                             const LogitSource& src, int32_t* topk_ids, float* topk_w,
+                             int32_t* counts, int32_t* offsets, int32_t* sorted_pairs,
+                             int32_t* active, int32_t* n_active, int32_t* tile_offsets,
+                             int32_t* pair_pos, int mfma_rows, hipStream_t stream,
+                             const RowBias& rb) {
+  if (tokens == 0) return hipSuccess;
+  launch(topk_group_kernel, dim3(1 + bias_blocks(rb, tokens, kGroupThreads / 64)),
+         dim3(kGroupThreads), stream, tokens, n_experts, top_k, renormalize, src, topk_ids, topk_w,
+         counts, offsets, sorted_pairs, active, n_active, tile_offsets, pair_pos, mfma_rows, rb);
   return hipGetLastError();
 }
 
