@@ -43,19 +43,34 @@ __device__ __forceinline__ float dot8_bf16(uint4 a, uint4 b, float c) {
                                          __builtin_bit_cast(bf16x2_t, b.w), c, false);
 }
 
-template <int kR, int kT>
+// With kNorm (K <= kNormMaxInputs) the input is RMSNorm(x + delta) * gain of
+// the rows X, formed by every workgroup for itself, in add_rmsnorm_kernel's
+// order of operations, while its weight rows are on their way: at one to four
+// tokens the norm as a launch of its own cost 3.6 us per layer, here its reads
+// (8 KB per token) come from L2.  Workgroup 0 also writes x + delta to x_out.
+constexpr int kNormMaxInputs = 8 * kThreads;  // one 16-byte chunk per thread
+struct NormInput {
+  const uint16_t* delta = nullptr;
+  const uint16_t* gain = nullptr;
+  uint16_t* x_out = nullptr;
+  float eps = 0.f;
+};
+
+template <int kR, int kT, bool kNorm>
 __global__ __launch_bounds__(kThreads) void dense_gemv_kernel(int N, int K, const uint16_t* X,
                                                               const uint16_t* W, const uint16_t* C,
-                                                              void* Y, int out_f32) {
+                                                              void* Y, int out_f32, NormInput nm) {
+  __shared__ uint4 xs[kNorm ? kT : 1][kNorm ? kThreads : 1];
+  __shared__ float red[kNorm ? kT : 1][kThreads / 64];
   const int lane = threadIdx.x & 63;
   const int n0 = (blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * kR;
-  if (n0 >= N) return;
+  if (!kNorm && n0 >= N) return;
   float acc[kR][kT];
 #pragma unroll
   for (int r = 0; r < kR; ++r)
 #pragma unroll
     for (int t = 0; t < kT; ++t) acc[r][t] = 0.f;
-  for (int k0 = 8 * lane; k0 < K; k0 += 512 * kDenseUnroll) {
+  for (int k0 = 8 * lane; k0 < (kNorm ? 8 * lane + 1 : K); k0 += 512 * kDenseUnroll) {
     uint4 w[kDenseUnroll][kR], x[kDenseUnroll][kT];
 #pragma unroll
     for (int u = 0; u < kDenseUnroll; ++u) {
@@ -66,9 +81,76 @@ __global__ __launch_bounds__(kThreads) void dense_gemv_kernel(int N, int K, cons
           const int n = min(n0 + r, N - 1);  // rows past N repeat the last (not stored)
           w[u][r] = *reinterpret_cast<const uint4*>(W + (int64_t)n * K + k);
         }
+        if constexpr (!kNorm) {
 #pragma unroll
-        for (int t = 0; t < kT; ++t) x[u][t] = *reinterpret_cast<const uint4*>(X + (int64_t)t * K + k);
+          for (int t = 0; t < kT; ++t) x[u][t] = *reinterpret_cast<const uint4*>(X + (int64_t)t * K + k);
+        }
       }
+    }
+    if constexpr (kNorm) {
+      // Thread i: chunk i of every row.
+      const int i = threadIdx.x;
+      const bool has = 8 * i < K;
+      float v[kT][8];
+      uint4 gv = make_uint4(0, 0, 0, 0), xv[kT], dv[kT];
+      if (has) {
+        gv = reinterpret_cast<const uint4*>(nm.gain)[i];
+#pragma unroll
+        for (int t = 0; t < kT; ++t) {
+          xv[t] = reinterpret_cast<const uint4*>(X + (int64_t)t * K)[i];
+          if (nm.delta) dv[t] = reinterpret_cast<const uint4*>(nm.delta + (int64_t)t * K)[i];
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < kT; ++t) {
+        float ss = 0.f;
+        if (has) {
+          uint32_t xw[4] = {xv[t].x, xv[t].y, xv[t].z, xv[t].w};
+          if (nm.delta) {
+            const uint32_t dw[4] = {dv[t].x, dv[t].y, dv[t].z, dv[t].w};
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+              const float lo = bf16_to_f32(xw[p] & 0xffffu) + bf16_to_f32(dw[p] & 0xffffu);
+              const float hi = bf16_to_f32(xw[p] >> 16) + bf16_to_f32(dw[p] >> 16);
+              xw[p] = f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
+            }
+            if (blockIdx.x == 0 && nm.x_out)
+              reinterpret_cast<uint4*>(nm.x_out + (int64_t)t * K)[i] = make_uint4(xw[0], xw[1], xw[2], xw[3]);
+          }
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            v[t][2 * p] = bf16_to_f32(xw[p] & 0xffffu);
+            v[t][2 * p + 1] = bf16_to_f32(xw[p] >> 16);
+            ss = fmaf(v[t][2 * p], v[t][2 * p], ss);
+            ss = fmaf(v[t][2 * p + 1], v[t][2 * p + 1], ss);
+          }
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
+        if (lane == 0) red[t][threadIdx.x >> 6] = ss;
+      }
+      __syncthreads();
+      if (has) {
+        const uint32_t gw[4] = {gv.x, gv.y, gv.z, gv.w};
+#pragma unroll
+        for (int t = 0; t < kT; ++t) {
+          const float sum = (red[t][0] + red[t][1]) + (red[t][2] + red[t][3]);
+          const float inv = 1.0f / sqrtf(sum / (float)K + nm.eps);
+          uint32_t o[4];
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            const float lo = v[t][2 * p] * inv * bf16_to_f32(gw[p] & 0xffffu);
+            const float hi = v[t][2 * p + 1] * inv * bf16_to_f32(gw[p] >> 16);
+            o[p] = f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
+          }
+          xs[t][i] = make_uint4(o[0], o[1], o[2], o[3]);
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kDenseUnroll; ++u)
+#pragma unroll
+        for (int t = 0; t < kT; ++t) x[u][t] = xs[t][lane + 64 * u];
     }
 #pragma unroll
     for (int u = 0; u < kDenseUnroll; ++u) {
@@ -318,18 +400,195 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(int H, int pos0, co
   }
 }
 
+// Rotary positions, cache append and causal attention of a decode step (T <=
+// kDenseMaxTokens) in one launch, one workgroup of 16 wavefronts per (head,
+// token t).  Its query and the keys of tokens 0 .. t are rotated here (angles
+// as in rope_kv_kernel, in fp64), token t's key and value appended to the
+// cache; keys and values of the call's own tokens come from qkv, so no
+// workgroup reads what another appends.
+// Bound by latency on H workgroups: a group of Dh/8 lanes takes a key per
+// stripe and pass, its 16-byte chunks of eight keys and eight values issued
+// before anything else (512 keys at Dh 128), the rotation running meanwhile;
+// each group keeps a running maximum, sum and output (fp32), combined over
+// the groups once at the end.  At 302 keys and 16 heads this and the rotation
+// took 11.4 + 4.2 us as two launches of 4-wavefront workgroups.
+constexpr int kAttnThreads = 1024;
+template <int kDh>
+__global__ __launch_bounds__(kAttnThreads) void step_attention_kernel(
+    int H, int pos0, double log_base, const uint16_t* qkv, uint16_t* k_cache, uint16_t* v_cache,
+    uint16_t* out) {
+  constexpr int kChunks = kDh / 8;
+  constexpr int kStripes = kAttnThreads / kChunks;
+  constexpr int kWavesA = kAttnThreads / 64;
+  constexpr int kAhead = 8;
+  constexpr int half = kDh / 2;
+  __shared__ __attribute__((aligned(16))) uint16_t qs[kDh];
+  __shared__ __attribute__((aligned(16))) uint16_t ks[kDenseMaxTokens][kDh];
+  __shared__ float part[kWavesA][kDh];
+  __shared__ float red_m[kWavesA], red_l[kWavesA];
+  const int h = blockIdx.x, t = blockIdx.y;
+  const int d = H * kDh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int chunk = tid % kChunks, stripe = tid / kChunks;
+  const uint16_t* kcol = k_cache + h * kDh + chunk * 8;
+  const uint16_t* vcol = v_cache + h * kDh + chunk * 8;
+  uint4 ka[kAhead], va[kAhead];
+  auto load_round = [&](int j0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int j = j0 + stripe + u * kStripes;
+      if (j < pos0) ka[u] = *reinterpret_cast<const uint4*>(kcol + (int64_t)j * d);
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int j = j0 + stripe + u * kStripes;
+      if (j < pos0) va[u] = *reinterpret_cast<const uint4*>(vcol + (int64_t)j * d);
+    }
+  };
+  load_round(0);
+  // Rotation: (token 0 .. t, pair i) over the threads.
+  for (int x = tid; x < (t + 1) * half; x += kAttnThreads) {
+    const int tt = x / half, i = x % half;
+    const double ang = (double)(pos0 + tt) * exp(-2.0 * (double)i / (double)kDh * log_base);
+    double sn, cn;
+    sincos(ang, &sn, &cn);
+    const float c = (float)cn, s = (float)sn;
+    const uint16_t* row = qkv + (int64_t)tt * 3 * d + h * kDh + i;
+    if (tt == t) {
+      const float qa = bf16_to_f32(row[0]), qb = bf16_to_f32(row[half]);
+      qs[i] = (uint16_t)f32_to_bf16_rne(qa * c - qb * s);
+      qs[i + half] = (uint16_t)f32_to_bf16_rne(qb * c + qa * s);
+    }
+    const float xa = bf16_to_f32(row[d]), xb = bf16_to_f32(row[d + half]);
+    const uint16_t ra = (uint16_t)f32_to_bf16_rne(xa * c - xb * s);
+    const uint16_t rb = (uint16_t)f32_to_bf16_rne(xb * c + xa * s);
+    ks[tt][i] = ra;
+    ks[tt][i + half] = rb;
+    if (tt == t) {
+      uint16_t* kc = k_cache + (int64_t)(pos0 + t) * d + h * kDh + i;
+      kc[0] = ra;
+      kc[half] = rb;
+    }
+  }
+  // Value of token `stripe` of this call for its own key; token t's is appended.
+  uint4 vn = make_uint4(0, 0, 0, 0);
+  if (stripe <= t) {
+    vn = *reinterpret_cast<const uint4*>(qkv + (int64_t)stripe * 3 * d + 2 * d + h * kDh + chunk * 8);
+    if (stripe == t) *reinterpret_cast<uint4*>(v_cache + (int64_t)(pos0 + t) * d + h * kDh + chunk * 8) = vn;
+  }
+  __syncthreads();
+  const uint4 q = *reinterpret_cast<const uint4*>(&qs[8 * chunk]);
+  const float scale = 1.0f / sqrtf((float)kDh);
+  // q . k over the group's lanes (every lane gets it).
+  auto score_of = [&](const uint4& k) __attribute__((always_inline)) -> float {
+    float v = dot8_bf16(k, q, 0.f);
+#pragma unroll
+    for (int o = 1; o < kChunks; o <<= 1) v += __shfl_xor(v, o);
+    return v * scale;
+  };
+  float m = -INFINITY, l = 0.f;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  auto add_value = [&](const uint4& v, float p) __attribute__((always_inline)) {
+    const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      acc[2 * e] = fmaf(p, bf16_to_f32(vw[e] & 0xffffu), acc[2 * e]);
+      acc[2 * e + 1] = fmaf(p, bf16_to_f32(vw[e] >> 16), acc[2 * e + 1]);
+    }
+  };
+  // Raise the running maximum to at least mx (finite) and rescale.
+  auto raise = [&](float mx) __attribute__((always_inline)) {
+    const float mn = fmaxf(m, mx);
+    const float f = expf(m - mn);
+    m = mn;
+    l *= f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] *= f;
+  };
+  for (int j0 = 0; j0 < pos0; j0 += kAhead * kStripes) {
+    if (j0) load_round(j0);
+    float sc[kAhead], mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const bool ok = j0 + stripe + u * kStripes < pos0;  // the same in all lanes of a group
+      sc[u] = -INFINITY;
+      if (ok) sc[u] = score_of(ka[u]);
+      mx = fmaxf(mx, sc[u]);
+    }
+    if (j0 + stripe < pos0) {
+      raise(mx);
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (j0 + stripe + u * kStripes < pos0) {
+          const float p = expf(sc[u] - m);
+          l += p;
+          add_value(va[u], p);
+        }
+    }
+  }
+  if (stripe <= t) {
+    const float s = score_of(*reinterpret_cast<const uint4*>(&ks[stripe][8 * chunk]));
+    raise(s);
+    const float p = expf(s - m);
+    l += p;
+    add_value(vn, p);
+  }
+  // Combine the groups: workgroup maximum, then rescaled sums over the
+  // wavefront's groups (butterfly) and over the wavefronts in order.
+  float wm = m;
+#pragma unroll
+  for (int o = kChunks; o < 64; o <<= 1) wm = fmaxf(wm, __shfl_xor(wm, o));
+  if (lane == 0) red_m[wave] = wm;
+  __syncthreads();
+  float mall = red_m[0];
+#pragma unroll
+  for (int w = 1; w < kWavesA; ++w) mall = fmaxf(mall, red_m[w]);
+  const float f = expf(m - mall);  // 0 for a group without keys (m = -inf)
+  l *= f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] *= f;
+#pragma unroll
+  for (int o = kChunks; o < 64; o <<= 1) {
+    l += __shfl_xor(l, o);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o);
+  }
+  if (lane < kChunks) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) part[wave][8 * chunk + e] = acc[e];
+    if (lane == 0) red_l[wave] = l;
+  }
+  __syncthreads();
+  if (tid < kDh) {
+    float o = 0.f, sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWavesA; ++w) {
+      o += part[w][tid];
+      sum += red_l[w];
+    }
+    out[(int64_t)t * d + h * kDh + tid] = (uint16_t)f32_to_bf16_rne(o / sum);
+  }
+}
+
 // Greedy next token: index of the largest logit, ties to the lower index.
 __global__ __launch_bounds__(1024) void argmax_kernel(int V, const float* logits, int32_t* out) {
   __shared__ float bv[16];
   __shared__ int bi[16];
   float best = -INFINITY;
   int idx = 0x7fffffff;
-  for (int i = threadIdx.x; i < V; i += 1024) {
-    const float v = logits[i];
-    if (v > best) {
-      best = v;
-      idx = i;
-    }
+  // One workgroup, so the loads of 16 logits per thread go out together: one
+  // at a time they took 16.8 us at 50,304 logits.
+  constexpr int kAhead = 16;
+  for (int i0 = threadIdx.x; i0 < V; i0 += 1024 * kAhead) {
+    float v[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) v[u] = logits[min(i0 + 1024 * u, V - 1)];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (v[u] > best) {  // ascending indices; a repeat of the last never exceeds it
+        best = v[u];
+        idx = min(i0 + 1024 * u, V - 1);
+      }
   }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
@@ -421,38 +680,43 @@ struct emoe_decoder {
 
 namespace {
 
+// Rows per wavefront of the GEMV: two when that still gives every CU a
+// workgroup or two, else one.
+template <bool kNorm>
+int32_t dense_gemv(int T, int N, int K, const uint16_t* X, const uint16_t* W, const uint16_t* C,
+                   void* Y, bool out_f32, const NormInput& nm, hipStream_t stream) {
+  constexpr int kWavesPer = kThreads / 64;
+  const int per_wave = (N + 2 * kWavesPer - 1) / (2 * kWavesPer) >= 256 ? 2 : 1;
+  const uint16_t* c = out_f32 ? nullptr : C;
+  const int f32 = out_f32 ? 1 : 0;
+  const dim3 grid((N + per_wave * kWavesPer - 1) / (per_wave * kWavesPer));
+#define DENSE_CASE(R, TT)                                                                         \
+  hipLaunchKernelGGL((dense_gemv_kernel<R, TT, kNorm>), grid, dim3(kThreads), 0, stream, N, K, X, \
+                     W, c, Y, f32, nm)
+  switch ((per_wave == 2 ? 8 : 0) + T) {
+    case 1: DENSE_CASE(1, 1); break;
+    case 2: DENSE_CASE(1, 2); break;
+    case 3: DENSE_CASE(1, 3); break;
+    case 4: DENSE_CASE(1, 4); break;
+    case 9: DENSE_CASE(2, 1); break;
+    case 10: DENSE_CASE(2, 2); break;
+    case 11: DENSE_CASE(2, 3); break;
+    default: DENSE_CASE(2, 4); break;
+  }
+#undef DENSE_CASE
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return report_error(EMOE_EHIP, "dense_gemv_kernel launch: %s", hipGetErrorString(e));
+  return EMOE_OK;
+}
+
 // Y[T][N] (+ C) = X[T][K] W[N][K]^T with bf16 inputs, fp32 accumulation.
 // out_f32 selects an fp32 output (C unused); otherwise bf16 out with
-// Y = X W^T + C when C is given.
+// Y = X W^T + C when C is given.  Decode steps take the weight-streaming
+// GEMV, prompts rocBLAS.
 int32_t dense(emoe_decoder* dec, int T, int N, int K, const uint16_t* X, const uint16_t* W,
               const uint16_t* C, void* Y, bool out_f32, hipStream_t stream) {
-  if (T <= kDenseMaxTokens && K % 8 == 0) {
-    // Decode steps: the weight-streaming GEMV, two rows per wavefront when
-    // that still gives every CU a workgroup or two, else one.
-    const int per_wg_2 = 2 * (kThreads / 64);
-    const bool two = (N + per_wg_2 - 1) / per_wg_2 >= 256;
-    const int per_wg = two ? per_wg_2 : kThreads / 64;
-    const dim3 grid((N + per_wg - 1) / per_wg);
-    const uint16_t* c = out_f32 ? nullptr : C;
-    const int f32 = out_f32 ? 1 : 0;
-#define DENSE_CASE(R, TT)                                                                        \
-  hipLaunchKernelGGL((dense_gemv_kernel<R, TT>), grid, dim3(kThreads), 0, stream, N, K, X, W, c, Y, \
-                     f32)
-    switch ((two ? 8 : 0) + T) {
-      case 1: DENSE_CASE(1, 1); break;
-      case 2: DENSE_CASE(1, 2); break;
-      case 3: DENSE_CASE(1, 3); break;
-      case 4: DENSE_CASE(1, 4); break;
-      case 9: DENSE_CASE(2, 1); break;
-      case 10: DENSE_CASE(2, 2); break;
-      case 11: DENSE_CASE(2, 3); break;
-      default: DENSE_CASE(2, 4); break;
-    }
-#undef DENSE_CASE
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return report_error(EMOE_EHIP, "dense_gemv_kernel launch: %s", hipGetErrorString(e));
-    return EMOE_OK;
-  }
+  if (T <= kDenseMaxTokens && K % 8 == 0)
+    return dense_gemv<false>(T, N, K, X, W, C, Y, out_f32, NormInput(), stream);
   const float alpha = 1.0f, beta = (C && !out_f32) ? 1.0f : 0.0f;
   const rocblas_datatype io = out_f32 ? rocblas_datatype_f32_r : rocblas_datatype_bf16_r;
   const void* c = (C && !out_f32) ? static_cast<const void*>(C) : static_cast<const void*>(Y);
@@ -561,23 +825,44 @@ int32_t emoe_decoder_forward(emoe_decoder* dec, const int32_t* tokens, int32_t T
   const uint16_t* delta = nullptr;
   const size_t kv_layer = (size_t)2 * D.max_positions * d;
   int32_t st;
+  // Decode steps (one to four tokens) take the norm into the QKV projection
+  // and the rotation into the attention; wider rows than one chunk per thread
+  // keep the norm's own launch.
+  const bool norm_in_gemv = d <= kNormMaxInputs;
+  const bool step = T <= kDenseMaxTokens;
+  const double log_base = log((double)D.rope_base);
   for (int l = 0; l < D.n_layers; ++l) {
     uint16_t* kc = dec->kv + (size_t)l * kv_layer;
     uint16_t* vc = kc + (size_t)D.max_positions * d;
-    DEC_LAUNCH(add_rmsnorm_kernel, dim3(T), dim3(kThreads), 0, stream, d, xa, delta,
-               dec->attn_norm[l], D.rms_eps, n);
-    if ((st = dense(dec, T, 3 * d, d, n, dec->wqkv[l], nullptr, qkv, false, stream))) return st;
-    DEC_LAUNCH(rope_kv_kernel, dim3(T), dim3(kThreads), 0, stream, H, Dh, pos0, D.rope_base, qkv,
-               kc, vc);
-    if (Dh == 64)
-      DEC_LAUNCH(attention_kernel<64>, dim3(H, T), dim3(kThreads), 0, stream, H, pos0, qkv, kc, vc,
-                 attn);
-    else if (Dh == 128)
-      DEC_LAUNCH(attention_kernel<128>, dim3(H, T), dim3(kThreads), 0, stream, H, pos0, qkv, kc,
-                 vc, attn);
-    else
-      DEC_LAUNCH(attention_kernel<256>, dim3(H, T), dim3(kThreads), 0, stream, H, pos0, qkv, kc,
-                 vc, attn);
+    if (step && norm_in_gemv) {
+      const NormInput nm{delta, dec->attn_norm[l], delta ? xb : nullptr, D.rms_eps};
+      if ((st = dense_gemv<true>(T, 3 * d, d, xa, dec->wqkv[l], nullptr, qkv, false, nm, stream)))
+        return st;
+      if (delta) std::swap(xa, xb);  // xa is x + delta
+    } else {
+      DEC_LAUNCH(add_rmsnorm_kernel, dim3(T), dim3(kThreads), 0, stream, d, xa, delta,
+                 dec->attn_norm[l], D.rms_eps, n);
+      if ((st = dense(dec, T, 3 * d, d, n, dec->wqkv[l], nullptr, qkv, false, stream))) return st;
+    }
+    if (step) {
+      const dim3 grid(H, T), block(kAttnThreads);
+      if (Dh == 64)
+        DEC_LAUNCH(step_attention_kernel<64>, grid, block, 0, stream, H, pos0, log_base, qkv, kc, vc, attn);
+      else if (Dh == 128)
+        DEC_LAUNCH(step_attention_kernel<128>, grid, block, 0, stream, H, pos0, log_base, qkv, kc, vc, attn);
+      else
+        DEC_LAUNCH(step_attention_kernel<256>, grid, block, 0, stream, H, pos0, log_base, qkv, kc, vc, attn);
+    } else {
+      DEC_LAUNCH(rope_kv_kernel, dim3(T), dim3(kThreads), 0, stream, H, Dh, pos0, D.rope_base, qkv,
+                 kc, vc);
+      const dim3 grid(H, T), block(kThreads);
+      if (Dh == 64)
+        DEC_LAUNCH(attention_kernel<64>, grid, block, 0, stream, H, pos0, qkv, kc, vc, attn);
+      else if (Dh == 128)
+        DEC_LAUNCH(attention_kernel<128>, grid, block, 0, stream, H, pos0, qkv, kc, vc, attn);
+      else
+        DEC_LAUNCH(attention_kernel<256>, grid, block, 0, stream, H, pos0, qkv, kc, vc, attn);
+    }
     if ((st = dense(dec, T, d, d, attn, dec->wo[l], xa, xb, false, stream))) return st;  // x += attn Wo^T
     std::swap(xa, xb);
     DEC_LAUNCH(add_rmsnorm_kernel, dim3(T), dim3(kThreads), 0, stream, d, xa, nullptr,
@@ -587,11 +872,17 @@ int32_t emoe_decoder_forward(emoe_decoder* dec, const int32_t* tokens, int32_t T
       return st;
     delta = moe_y;
   }
-  DEC_LAUNCH(add_rmsnorm_kernel, dim3(T), dim3(kThreads), 0, stream, d, xa, delta, dec->final_norm,
-             D.rms_eps, n);
-  if ((st = dense(dec, 1, D.vocab, d, n + (size_t)(T - 1) * d, dec->lm_head, nullptr, logits, true,
-                  stream)))
-    return st;
+  // Only the last token's logits are asked for.
+  const size_t last = (size_t)(T - 1) * d;
+  if (norm_in_gemv) {
+    const NormInput nm{delta + last, dec->final_norm, nullptr, D.rms_eps};
+    if ((st = dense_gemv<true>(1, D.vocab, d, xa + last, dec->lm_head, nullptr, logits, true, nm, stream)))
+      return st;
+  } else {
+    DEC_LAUNCH(add_rmsnorm_kernel, dim3(1), dim3(kThreads), 0, stream, d, xa + last, delta + last,
+               dec->final_norm, D.rms_eps, n);
+    if ((st = dense(dec, 1, D.vocab, d, n, dec->lm_head, nullptr, logits, true, stream))) return st;
+  }
   DEC_LAUNCH(argmax_kernel, dim3(1), dim3(1024), 0, stream, D.vocab, logits, next_token);
   return EMOE_OK;
 }
