@@ -14,10 +14,17 @@
 //    of each) go straight into registers; both one group ahead of their use,
 //    in a ring of two stages.  The 16-byte chunks of a token row are
 //    XOR-swizzled by the row index, which makes the MFMA A-fragment reads free
-//    of bank conflicts.  The per-row bias of the group is one contiguous
-//    256-byte run and the wavefront's 64 scales one 8-byte load per lane, so a
-//    group costs each wavefront 10 vector memory instructions, issued in four
-//    parts spread over the previous group's k-steps.
+//    of bank conflicts.  The wavefront's 64 scales are one 8-byte load per
+//    lane, so a group costs each wavefront 9 vector memory instructions,
+//    issued in four parts spread over the previous group's k-steps; a tile of
+//    at most 32 rows leaves out the copies of the others.
+//  - A tile's start is a chain of latencies (its expert and rows, its token
+//    ids, its first group): one round for the first, one id per lane passed
+//    on by lane moves, and the bias table copied straight into LDS beside the
+//    first group.  At 16 and 113 tokens, where each workgroup has one tile,
+//    gate/up took 29.2 and 32.7 us and down 16.8 and 19.1 before these and the
+//    shorter copies, 27.6 and 31.0, 15.5 and 17.9 now; 777 tokens 73.5 and
+//    42.4 against 71.5 and 41.3.
 //  - Each dword of codes expands in registers to one B operand of
 //    v_mfma_f32_16x16x32_bf16 (record layout in common.h): the codes enter as
 //    bf16 (128 + u), and the chain of four MFMAs of a group starts from the
@@ -166,8 +173,6 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
   StageT& st1 = stage_mem<kWaves, 1>();
   // The tile's bias, [group][row], gathered once in the prologue.
   __shared__ __attribute__((aligned(16))) float bias_lds[kMaxBiasGroups][kRows];
-  // Down: the pair id of each tile row, read in the prologue for the epilogue.
-  __shared__ int pair_lds[kRows];
 
   const int tid = threadIdx.x;
   const int lane = lane_id();
@@ -187,17 +192,39 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
   auto run_item = [&](const int item) __attribute__((always_inline)) {
   const int tile = item / n_ctiles;
   const int ctile = item - tile * n_ctiles;
-  // Row tile -> expert (largest e with tile_offsets[e] <= tile).
-  int lo = 0, hi = n_experts;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (gv.tile_offsets[mid] <= tile) lo = mid; else hi = mid;
+  // Row tile -> expert: the largest e with tile_offsets[e] <= tile, counted
+  // over all experts at once (lane l of round c holds expert 64c + l), together
+  // with its rows, so a tile's place costs one memory latency; a binary search
+  // and the offsets after it were a chain of eight.
+  int expert = -1, row0 = 0, rows = 0;
+  {
+    constexpr int kRounds = (EMOE_MAX_EXPERTS + 63) / 64;
+    int to[kRounds], of0[kRounds], of1[kRounds];
+#pragma unroll
+    for (int c = 0; c < kRounds; ++c) {
+      const int e = min(64 * c + lane, n_experts - 1);
+      if (64 * c < n_experts) {
+        to[c] = gv.tile_offsets[e];
+        of0[c] = gv.offsets[e];
+        of1[c] = gv.offsets[e + 1];
+      }
+    }
+    int below = 0;
+#pragma unroll
+    for (int c = 0; c < kRounds; ++c)
+      if (64 * c < n_experts)
+        below += __popcll(__ballot(64 * c + lane < n_experts && to[c] <= tile));
+    expert = below - 1;  // tile_offsets[0] = 0
+#pragma unroll
+    for (int c = 0; c < kRounds; ++c)
+      if (64 * c < n_experts && (expert >> 6) == c) {
+        const int l = expert & 63;
+        row0 = __builtin_amdgcn_readlane(of0[c], l) + kRows * (tile - __builtin_amdgcn_readlane(to[c], l));
+        rows = min(kRows, __builtin_amdgcn_readlane(of1[c], l) - row0);
+      }
   }
-  const int expert = lo;
   const int slot = wave.n < 0 ? expert : (int)wave.slot_of[expert];
   if (slot < 0) return;  // expert not in this wave
-  const int row0 = gv.offsets[expert] + kRows * (tile - gv.tile_offsets[expert]);
-  const int rows = min(kRows, gv.offsets[expert + 1] - row0);
 
   const int K = kGateUp ? d : f;
   const int G = K / kGroup;
@@ -216,27 +243,28 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
   const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(x, x_bytes);
   const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(rec, (uint32_t)record_bytes);
 
-  // Source row of a tile row (rows past the tile's end repeat its last row;
-  // their results are discarded).
-  auto src_row = [&](int m) __attribute__((always_inline)) -> int {
-    const int mc = min(m, rows - 1);
-    return kGateUp ? gv.sorted_pairs[row0 + mc] / top_k : row0 + mc;
-  };
-  // Token-row chunks this thread copies: stage chunk (kDma*wi + j)*64 + lane
-  // is row m = 4*(kDma*wi + j) + lane/16, slot p = lane%16, holding chunk
-  // p ^ (m%16).
+  // Source row (a token for gate/up, a grouped position for down) of tile row
+  // `lane`; rows past the tile's end repeat its last row, their results are
+  // discarded.  Other rows' come from their lanes.
+  const int mc = min(lane, rows - 1);
+  const int pair = gv.sorted_pairs[row0 + mc];  // gate/up: for its token; down: for the epilogue
+  const int src = kGateUp ? pair / top_k : row0 + mc;
+  // Token-row chunks this thread copies: copy j of a wavefront fills 64 chunks
+  // of rows 32*(j/2) + 8*wi + 4*(j%2) + lane/16 (so the copies of rows 32 on
+  // are j >= 2), chunk position p = lane%16 holding chunk p ^ (m%16).
   uint32_t a_off[kDma];
 #pragma unroll
   for (int j = 0; j < kDma; ++j) {
-    const int m = 4 * (kDma * wi + j) + (lane >> 4);
+    const int m = 32 * (j >> 1) + 8 * wi + 4 * (j & 1) + (lane >> 4);
     const int c = (lane & 15) ^ (m & 15);
-    a_off[j] = (uint32_t)src_row(m) * (uint32_t)(K * 2) + 16u * c;
+    a_off[j] = (uint32_t)__shfl(src, m) * (uint32_t)(K * 2) + 16u * c;
   }
-  // Bias gather: thread t fills row t % 64 of every kWaves-th group from
-  // t / 64 on; its source row (a token for gate/up, a grouped position for
-  // down) is known now, so the gather overlaps the first group's loads.
-  const int b_row = tid & (kRows - 1);
-  const int b_src = src_row(b_row);
+  // Bias gather straight into LDS: wavefront w copies every kWaves-th group's
+  // row of the table from w on, ahead of the first group's loads.
+  const __amdgpu_buffer_rsrc_t b_rsrc = make_rsrc(bias, x_bytes / (kGroup / 2));
+  const uint32_t b_off = kGateUp ? (uint32_t)src * (uint32_t)(G * 4) : (uint32_t)src * 4u;
+  const uint32_t b_step = kGateUp ? 4u : (uint32_t)pairs * 4u;
+  for (int gg = wi; gg < G; gg += kWaves) load_lds4(b_rsrc, &bias_lds[gg][0], b_off, (uint32_t)gg * b_step);
   const uint32_t w_off = (uint32_t)((kGateUp ? L.w13_codes : L.w2_codes) +
                                     (int64_t)rb0 * G * kTileBytes) + 16u * lane;
   // Scales of the wavefront's four row blocks for one group: 128 bytes, the
@@ -262,7 +290,8 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
     if constexpr (P < 2) {
 #pragma unroll
       for (int j = P * (kDma / 2); j < (P + 1) * (kDma / 2); ++j)
-        load_lds16(x_rsrc, &sm.a[(kDma * wi + j) * 64 * 8], a_off[j], (uint32_t)g * kGroup * 2);
+        load_lds16(x_rsrc, &sm.a[(32 * (j >> 1) + 8 * wi + 4 * (j & 1)) * kGroup], a_off[j],
+                   (uint32_t)g * kGroup * 2);
     } else {
 #pragma unroll
       for (int r = 2 * (P - 2); r < 2 * (P - 1); ++r)
@@ -274,7 +303,7 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
             uint2, __builtin_amdgcn_raw_buffer_load_b64(w_rsrc, (int)s_off, g * 128, 0));
     }
   };
-  static_assert(kDma % 2 == 0 && kNPW == 4, "four load parts");
+  static_assert(kDma == 4 && kWaves == 4 && kNPW == 4, "four load parts, 32 rows per two copies");
   auto issue = [&](int g, auto stage) __attribute__((always_inline)) {
     issue_part(g, stage, std::integral_constant<int, 0>());
     issue_part(g, stage, std::integral_constant<int, 1>());
@@ -316,7 +345,8 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
       constexpr int i = decltype(ic)::value;
       if constexpr (kMore && kIssueFirst) {
         __builtin_amdgcn_sched_barrier(0);
-        issue_part(g + 1, Next(), ic);
+        // No rows past 32: their copies (part 1) stay out.
+        if constexpr (kMB > 2 || i != 1) issue_part(g + 1, Next(), ic);
         __builtin_amdgcn_sched_barrier(0);
       }
       bf16x8_t a[4];
@@ -373,10 +403,6 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
   using S1 = std::integral_constant<int, 1>;
 
   issue(0, S0());
-  // Gather the tile's bias while the first group loads.
-  for (int gg = wi; gg < G; gg += kWaves)
-    bias_lds[gg][b_row] = kGateUp ? bias[(int64_t)b_src * G + gg] : bias[(int64_t)gg * pairs + b_src];
-  if (!kGateUp && tid < kRows) pair_lds[tid] = gv.sorted_pairs[b_src];
   wait_loads<0>();
   barrier();
   // Groups 0 .. G-2 issue the next group; pairs of steps run in the loop.
@@ -413,7 +439,8 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
     constexpr int kStride = kActCols + 8;  // row pitch in bf16 (padded against bank conflicts)
     uint16_t* tile_act = reinterpret_cast<uint16_t*>(&st0);
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    for (int mi = 0; mi < 4; ++mi) {
+      if (16 * mi >= rows) break;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -423,6 +450,7 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
           tile_act[(16 * mi + 4 * quarter + j) * kStride + 16 * (2 * wi + p) + n_local] =
               (uint16_t)f32_to_bf16_rne(silu_fast(gv_) * uv);
         }
+    }
     barrier();
     // Thread t copies chunks (row t/R + (kThreads/R)q, column chunk t%R, with
     // R = kActCols/8 chunks per row) and sums each chunk; the 16 threads of
@@ -462,8 +490,9 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int m = 16 * mi + 4 * quarter + j;
+          const int pi = __shfl(pair, m);
           if (m < rows) {
-            float* out = pair_out_f32 + (int64_t)pair_lds[m] * d + 16 * rb0 + n_local;
+            float* out = pair_out_f32 + (int64_t)pi * d + 16 * rb0 + n_local;
 #pragma unroll
             for (int r = 0; r < kNPW; ++r) out[16 * r] = acc[r][mi][j];
           }
@@ -476,6 +505,7 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
     uint16_t* half1 = reinterpret_cast<uint16_t*>(&st1);
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi) {
+      if (16 * mi >= rows) break;
       uint16_t* t = mi < 2 ? half0 : half1;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -492,9 +522,9 @@ __global__ __launch_bounds__(Sh::kThreads, Sh::kBlocksPerCu) void grouped_mfma_k
     for (int q = 0; q < 8; ++q) {
       const int m = tid / R + (Sh::kThreads / R) * q;
       const uint16_t* t = m < 32 ? half0 : half1;
+      const int pi = __shfl(pair, m);
       if (m < rows && col < d) {
         const uint4 v = *reinterpret_cast<const uint4*>(&t[(m & 31) * kStride + 8 * cc]);
-        const int pi = pair_lds[m];
         *reinterpret_cast<uint4*>(pair_out + (int64_t)pi * d + col) = v;
       }
     }
