@@ -274,21 +274,57 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(int d, uint16_t* 
   }
 }
 
+// Angular frequencies base^(-2i/Dh) of a decoder, fp64, formed when it is made.
+struct RopeTable {
+  double inv[kMaxHeadDim / 2];
+};
+
+// cos and sin (fp32) of an angle 0 <= x <= 8192 in fp64: x - n pi/2 with pi/2
+// in two terms, then the Taylor polynomials to x^17 on [-pi/4, pi/4] (the
+// first omitted term is below 1e-16).  The library's pow, sincos and their
+// range reduction for any argument kept the few lanes that rotate a token busy
+// for most of the 4.2 us of rope_kv_kernel at one token.
+__device__ __forceinline__ void rope_cos_sin(double x, float& c, float& s) {
+  const double n = rint(x * 0.63661977236758134308);
+  double r = fma(-n, 1.5707963267948965580, x);
+  r = fma(-n, 6.1232339957367660359e-17, r);
+  const double z = r * r;
+  double ps = fma(z, 1.0 / 355687428096000.0, -1.0 / 1307674368000.0);
+  ps = fma(z, ps, 1.0 / 6227020800.0);
+  ps = fma(z, ps, -1.0 / 39916800.0);
+  ps = fma(z, ps, 1.0 / 362880.0);
+  ps = fma(z, ps, -1.0 / 5040.0);
+  ps = fma(z, ps, 1.0 / 120.0);
+  ps = fma(z, ps, -1.0 / 6.0);
+  const double sn = fma(r * z, ps, r);
+  double pc = fma(z, 1.0 / 20922789888000.0, -1.0 / 87178291200.0);
+  pc = fma(z, pc, 1.0 / 479001600.0);
+  pc = fma(z, pc, -1.0 / 3628800.0);
+  pc = fma(z, pc, 1.0 / 40320.0);
+  pc = fma(z, pc, -1.0 / 720.0);
+  pc = fma(z, pc, 1.0 / 24.0);
+  pc = fma(z, pc, -0.5);
+  const double cn = fma(z, pc, 1.0);
+  const int k = (int)n & 3;
+  const double a = (k & 1) ? sn : cn, b = (k & 1) ? cn : sn;
+  c = (float)((k == 1 || k == 2) ? -a : a);
+  s = (float)(k >= 2 ? -b : b);
+}
+
 // Rotary positions on q (in place in qkv) and k, and the cache append of k
 // and v, for token t at position pos0 + t.  Element i < Dh/2 of a head pairs
 // with i + Dh/2; the angle p * base^(-2i/Dh) and its sine and cosine are
 // taken in fp64, the rotation in fp32.  qkv row: [q (H*Dh) | k | v].
-__global__ __launch_bounds__(kThreads) void rope_kv_kernel(int H, int Dh, int pos0, float base,
-                                                           uint16_t* qkv, uint16_t* k_cache,
+__global__ __launch_bounds__(kThreads) void rope_kv_kernel(int H, int Dh, int pos0,
+                                                           RopeTable rope, uint16_t* qkv,
+                                                           uint16_t* k_cache,
                                                            uint16_t* v_cache) {
   __shared__ float cs[kMaxHeadDim / 2][2];
   const int t = blockIdx.x;
   const int d = H * Dh, half = Dh / 2;
   const int p = pos0 + t;
   for (int i = threadIdx.x; i < half; i += kThreads) {
-    const double ang = (double)p * pow((double)base, -2.0 * (double)i / (double)Dh);
-    cs[i][0] = (float)cos(ang);
-    cs[i][1] = (float)sin(ang);
+    rope_cos_sin((double)p * rope.inv[i], cs[i][0], cs[i][1]);
   }
   __syncthreads();
   uint16_t* q = qkv + (int64_t)t * 3 * d;
@@ -407,20 +443,20 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(int H, int pos0, co
 // cache; keys and values of the call's own tokens come from qkv, so no
 // workgroup reads what another appends.
 // Bound by latency on H workgroups: a group of Dh/8 lanes takes a key per
-// stripe and pass, its 16-byte chunks of eight keys and eight values issued
-// before anything else (512 keys at Dh 128), the rotation running meanwhile;
+// stripe and pass, its 16-byte chunks of six keys and six values issued
+// before anything else (384 keys at Dh 128; eight of each spilled), the rotation running meanwhile;
 // each group keeps a running maximum, sum and output (fp32), combined over
 // the groups once at the end.  At 302 keys and 16 heads this and the rotation
-// took 11.4 + 4.2 us as two launches of 4-wavefront workgroups.
+// took 11.4 + 4.2 us as two launches of 4-wavefront workgroups, now 9.2.
 constexpr int kAttnThreads = 1024;
 template <int kDh>
 __global__ __launch_bounds__(kAttnThreads) void step_attention_kernel(
-    int H, int pos0, double log_base, const uint16_t* qkv, uint16_t* k_cache, uint16_t* v_cache,
+    int H, int pos0, RopeTable rope, const uint16_t* qkv, uint16_t* k_cache, uint16_t* v_cache,
     uint16_t* out) {
   constexpr int kChunks = kDh / 8;
   constexpr int kStripes = kAttnThreads / kChunks;
   constexpr int kWavesA = kAttnThreads / 64;
-  constexpr int kAhead = 8;
+  constexpr int kAhead = 6;
   constexpr int half = kDh / 2;
   __shared__ __attribute__((aligned(16))) uint16_t qs[kDh];
   __shared__ __attribute__((aligned(16))) uint16_t ks[kDenseMaxTokens][kDh];
@@ -449,10 +485,8 @@ __global__ __launch_bounds__(kAttnThreads) void step_attention_kernel(
   // Rotation: (token 0 .. t, pair i) over the threads.
   for (int x = tid; x < (t + 1) * half; x += kAttnThreads) {
     const int tt = x / half, i = x % half;
-    const double ang = (double)(pos0 + tt) * exp(-2.0 * (double)i / (double)kDh * log_base);
-    double sn, cn;
-    sincos(ang, &sn, &cn);
-    const float c = (float)cn, s = (float)sn;
+    float c, s;
+    rope_cos_sin((double)(pos0 + tt) * rope.inv[i], c, s);
     const uint16_t* row = qkv + (int64_t)tt * 3 * d + h * kDh + i;
     if (tt == t) {
       const float qa = bf16_to_f32(row[0]), qb = bf16_to_f32(row[half]);
@@ -675,6 +709,7 @@ struct emoe_decoder {
   std::vector<const uint16_t*> attn_norm, wqkv, wo, moe_norm, w_router;
   std::vector<emoe_cache*> caches;
   uint16_t* kv = nullptr;
+  RopeTable rope{};
   rocblas_handle blas = nullptr;
 };
 
@@ -779,6 +814,8 @@ int32_t emoe_decoder_create(const emoe_decoder_dims* dims, const emoe_decoder_we
   dec->w_router.assign(w->w_router, w->w_router + L);
   dec->caches.assign(caches, caches + L);
   dec->kv = static_cast<uint16_t*>(kv_cache);
+  for (int i = 0; i < dims->head_dim / 2; ++i)
+    dec->rope.inv[i] = std::pow((double)dims->rope_base, -2.0 * (double)i / (double)dims->head_dim);
   const rocblas_status rs = rocblas_create_handle(&dec->blas);
   if (rs != rocblas_status_success) {
     delete dec;
@@ -830,7 +867,6 @@ int32_t emoe_decoder_forward(emoe_decoder* dec, const int32_t* tokens, int32_t T
   // keep the norm's own launch.
   const bool norm_in_gemv = d <= kNormMaxInputs;
   const bool step = T <= kDenseMaxTokens;
-  const double log_base = log((double)D.rope_base);
   for (int l = 0; l < D.n_layers; ++l) {
     uint16_t* kc = dec->kv + (size_t)l * kv_layer;
     uint16_t* vc = kc + (size_t)D.max_positions * d;
@@ -847,13 +883,13 @@ int32_t emoe_decoder_forward(emoe_decoder* dec, const int32_t* tokens, int32_t T
     if (step) {
       const dim3 grid(H, T), block(kAttnThreads);
       if (Dh == 64)
-        DEC_LAUNCH(step_attention_kernel<64>, grid, block, 0, stream, H, pos0, log_base, qkv, kc, vc, attn);
+        DEC_LAUNCH(step_attention_kernel<64>, grid, block, 0, stream, H, pos0, dec->rope, qkv, kc, vc, attn);
       else if (Dh == 128)
-        DEC_LAUNCH(step_attention_kernel<128>, grid, block, 0, stream, H, pos0, log_base, qkv, kc, vc, attn);
+        DEC_LAUNCH(step_attention_kernel<128>, grid, block, 0, stream, H, pos0, dec->rope, qkv, kc, vc, attn);
       else
-        DEC_LAUNCH(step_attention_kernel<256>, grid, block, 0, stream, H, pos0, log_base, qkv, kc, vc, attn);
+        DEC_LAUNCH(step_attention_kernel<256>, grid, block, 0, stream, H, pos0, dec->rope, qkv, kc, vc, attn);
     } else {
-      DEC_LAUNCH(rope_kv_kernel, dim3(T), dim3(kThreads), 0, stream, H, Dh, pos0, D.rope_base, qkv,
+      DEC_LAUNCH(rope_kv_kernel, dim3(T), dim3(kThreads), 0, stream, H, Dh, pos0, dec->rope, qkv,
                  kc, vc);
       const dim3 grid(H, T), block(kThreads);
       if (Dh == 64)
