@@ -437,51 +437,63 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(int H, int pos0, co
 }
 
 // Rotary positions, cache append and causal attention of a decode step (T <=
-// kDenseMaxTokens) in one launch, one workgroup of 16 wavefronts per (head,
+// kDenseMaxTokens) in one launch, one workgroup of 8 wavefronts per (head,
 // token t).  Its query and the keys of tokens 0 .. t are rotated here (angles
 // as in rope_kv_kernel, in fp64), token t's key and value appended to the
 // cache; keys and values of the call's own tokens come from qkv, so no
-// workgroup reads what another appends.
-// Bound by latency on H workgroups: a group of Dh/8 lanes takes a key per
-// stripe and pass, its 16-byte chunks of six keys and six values issued
-// before anything else (384 keys at Dh 128; eight of each spilled), the rotation running meanwhile;
-// each group keeps a running maximum, sum and output (fp32), combined over
-// the groups once at the end.  At 302 keys and 16 heads this and the rotation
-// took 11.4 + 4.2 us as two launches of 4-wavefront workgroups, now 9.2.
-constexpr int kAttnThreads = 1024;
+// workgroup reads what another appends.  Every sum keeps attention_kernel's
+// order (a key's score by one thread, the weights' sum over 256 threads, the
+// output over 2048 / Dh stripes of keys), so both give the same bits.
+// Bound by latency on H workgroups: the first 512 keys' chunks (a key per
+// thread, spread over the wavefronts) and the first 20 values of every stripe
+// (four dimensions per thread) are on their way before the rotation starts
+// (16 wavefronts had 128 registers each, spilled them and took 22 us).  At 302 keys and 16 heads this and the rotation
+// took 11.4 + 4.2 us as two launches of 4-wavefront workgroups, now 10.3.
+constexpr int kAttnThreads = 512;
 template <int kDh>
 __global__ __launch_bounds__(kAttnThreads) void step_attention_kernel(
     int H, int pos0, RopeTable rope, const uint16_t* qkv, uint16_t* k_cache, uint16_t* v_cache,
     uint16_t* out) {
   constexpr int kChunks = kDh / 8;
-  constexpr int kStripes = kAttnThreads / kChunks;
-  constexpr int kWavesA = kAttnThreads / 64;
-  constexpr int kAhead = 6;
+  constexpr int kBlock = kChunks == 32 ? 8 : kChunks;  // key chunks held at a time
   constexpr int half = kDh / 2;
-  __shared__ __attribute__((aligned(16))) uint16_t qs[kDh];
+  constexpr int kQuads = kDh / 4;
+  constexpr int kStripes = kAttnThreads / kQuads;
+  static_assert(kStripes == kThreads / kChunks, "attention_kernel's stripes");
+  constexpr int kWavesA = kAttnThreads / 64;
+  constexpr int kVAhead = 20;
+  __shared__ float score[EMOE_DECODER_MAX_POSITIONS];
+  __shared__ __attribute__((aligned(16))) uint32_t qs[half];
   __shared__ __attribute__((aligned(16))) uint16_t ks[kDenseMaxTokens][kDh];
-  __shared__ float part[kWavesA][kDh];
-  __shared__ float red_m[kWavesA], red_l[kWavesA];
+  __shared__ float part[kStripes][kDh];
+  __shared__ float red[kWavesA], red_sum[4];
   const int h = blockIdx.x, t = blockIdx.y;
   const int d = H * kDh;
+  const int n = pos0 + t + 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int chunk = tid % kChunks, stripe = tid / kChunks;
-  const uint16_t* kcol = k_cache + h * kDh + chunk * 8;
-  const uint16_t* vcol = v_cache + h * kDh + chunk * 8;
-  uint4 ka[kAhead], va[kAhead];
-  auto load_round = [&](int j0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const int j = j0 + stripe + u * kStripes;
-      if (j < pos0) ka[u] = *reinterpret_cast<const uint4*>(kcol + (int64_t)j * d);
-    }
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const int j = j0 + stripe + u * kStripes;
-      if (j < pos0) va[u] = *reinterpret_cast<const uint4*>(vcol + (int64_t)j * d);
-    }
+  const uint16_t* khead = k_cache + h * kDh;
+  const int quad = tid % kQuads, stripe = tid / kQuads;
+  const uint16_t* vcol = v_cache + h * kDh + 4 * quad;
+  const uint16_t* vnew = qkv + 2 * d + h * kDh + 4 * quad;
+  auto load_value = [&](int j) __attribute__((always_inline)) -> uint2 {
+    const uint16_t* p = j < pos0 ? vcol + (int64_t)j * d : vnew + (int64_t)(j - pos0) * 3 * d;
+    return *reinterpret_cast<const uint2*>(p);
   };
-  load_round(0);
+  // This thread's keys: j0, j0 + 512, ..
+  const int j0 = lane * kWavesA + wave;
+  uint4 kv[kBlock];
+  auto load_key = [&](int j, int c0) __attribute__((always_inline)) {
+    const uint4* kr = reinterpret_cast<const uint4*>(khead + (int64_t)j * d) + c0;
+#pragma unroll
+    for (int c = 0; c < kBlock; ++c) kv[c] = kr[c];
+  };
+  if (j0 < pos0) load_key(j0, 0);
+  uint2 va[kVAhead];
+#pragma unroll
+  for (int u = 0; u < kVAhead; ++u) {
+    const int j = stripe + u * kStripes;
+    if (j < n) va[u] = load_value(j);
+  }
   // Rotation: (token 0 .. t, pair i) over the threads.
   for (int x = tid; x < (t + 1) * half; x += kAttnThreads) {
     const int tt = x / half, i = x % half;
@@ -490,8 +502,9 @@ __global__ __launch_bounds__(kAttnThreads) void step_attention_kernel(
     const uint16_t* row = qkv + (int64_t)tt * 3 * d + h * kDh + i;
     if (tt == t) {
       const float qa = bf16_to_f32(row[0]), qb = bf16_to_f32(row[half]);
-      qs[i] = (uint16_t)f32_to_bf16_rne(qa * c - qb * s);
-      qs[i + half] = (uint16_t)f32_to_bf16_rne(qb * c + qa * s);
+      uint16_t* q16 = reinterpret_cast<uint16_t*>(qs);
+      q16[i] = (uint16_t)f32_to_bf16_rne(qa * c - qb * s);
+      q16[i + half] = (uint16_t)f32_to_bf16_rne(qb * c + qa * s);
     }
     const float xa = bf16_to_f32(row[d]), xb = bf16_to_f32(row[d + half]);
     const uint16_t ra = (uint16_t)f32_to_bf16_rne(xa * c - xb * s);
@@ -504,102 +517,81 @@ __global__ __launch_bounds__(kAttnThreads) void step_attention_kernel(
       kc[half] = rb;
     }
   }
-  // Value of token `stripe` of this call for its own key; token t's is appended.
-  uint4 vn = make_uint4(0, 0, 0, 0);
-  if (stripe <= t) {
-    vn = *reinterpret_cast<const uint4*>(qkv + (int64_t)stripe * 3 * d + 2 * d + h * kDh + chunk * 8);
-    if (stripe == t) *reinterpret_cast<uint4*>(v_cache + (int64_t)(pos0 + t) * d + h * kDh + chunk * 8) = vn;
-  }
+  if (tid < half)
+    *reinterpret_cast<uint32_t*>(v_cache + (int64_t)(pos0 + t) * d + h * kDh + 2 * tid) =
+        *reinterpret_cast<const uint32_t*>(qkv + (int64_t)t * 3 * d + 2 * d + h * kDh + 2 * tid);
   __syncthreads();
-  const uint4 q = *reinterpret_cast<const uint4*>(&qs[8 * chunk]);
   const float scale = 1.0f / sqrtf((float)kDh);
-  // q . k over the group's lanes (every lane gets it).
-  auto score_of = [&](const uint4& k) __attribute__((always_inline)) -> float {
-    float v = dot8_bf16(k, q, 0.f);
+  float mx = -INFINITY;
+  for (int j = j0; j < n; j += kAttnThreads) {
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int c0 = 0; c0 < kChunks; c0 += kBlock) {
+      if (j >= pos0) {
+        const uint4* kr = reinterpret_cast<const uint4*>(ks[j - pos0]) + c0;
 #pragma unroll
-    for (int o = 1; o < kChunks; o <<= 1) v += __shfl_xor(v, o);
-    return v * scale;
-  };
-  float m = -INFINITY, l = 0.f;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto add_value = [&](const uint4& v, float p) __attribute__((always_inline)) {
-    const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
+        for (int c = 0; c < kBlock; ++c) kv[c] = kr[c];
+      } else if (j != j0 || c0 != 0) {
+        load_key(j, c0);
+      }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc[2 * e] = fmaf(p, bf16_to_f32(vw[e] & 0xffffu), acc[2 * e]);
-      acc[2 * e + 1] = fmaf(p, bf16_to_f32(vw[e] >> 16), acc[2 * e + 1]);
+      for (int c = 0; c < kBlock; ++c) {
+        const uint32_t kw[4] = {kv[c].x, kv[c].y, kv[c].z, kv[c].w};
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          acc[p] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, kw[p]),
+                                                   __builtin_bit_cast(bf16x2_t, qs[4 * (c0 + c) + p]),
+                                                   acc[p], false);
+      }
     }
-  };
-  // Raise the running maximum to at least mx (finite) and rescale.
-  auto raise = [&](float mx) __attribute__((always_inline)) {
-    const float mn = fmaxf(m, mx);
-    const float f = expf(m - mn);
-    m = mn;
-    l *= f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] *= f;
-  };
-  for (int j0 = 0; j0 < pos0; j0 += kAhead * kStripes) {
-    if (j0) load_round(j0);
-    float sc[kAhead], mx = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const bool ok = j0 + stripe + u * kStripes < pos0;  // the same in all lanes of a group
-      sc[u] = -INFINITY;
-      if (ok) sc[u] = score_of(ka[u]);
-      mx = fmaxf(mx, sc[u]);
-    }
-    if (j0 + stripe < pos0) {
-      raise(mx);
-#pragma unroll
-      for (int u = 0; u < kAhead; ++u)
-        if (j0 + stripe + u * kStripes < pos0) {
-          const float p = expf(sc[u] - m);
-          l += p;
-          add_value(va[u], p);
-        }
-    }
+    const float s = ((acc[0] + acc[1]) + (acc[2] + acc[3])) * scale;
+    score[j] = s;
+    mx = fmaxf(mx, s);
   }
-  if (stripe <= t) {
-    const float s = score_of(*reinterpret_cast<const uint4*>(&ks[stripe][8 * chunk]));
-    raise(s);
-    const float p = expf(s - m);
-    l += p;
-    add_value(vn, p);
-  }
-  // Combine the groups: workgroup maximum, then rescaled sums over the
-  // wavefront's groups (butterfly) and over the wavefronts in order.
-  float wm = m;
 #pragma unroll
-  for (int o = kChunks; o < 64; o <<= 1) wm = fmaxf(wm, __shfl_xor(wm, o));
-  if (lane == 0) red_m[wave] = wm;
+  for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+  if (lane == 0) red[wave] = mx;
   __syncthreads();
-  float mall = red_m[0];
+  mx = red[0];
 #pragma unroll
-  for (int w = 1; w < kWavesA; ++w) mall = fmaxf(mall, red_m[w]);
-  const float f = expf(m - mall);  // 0 for a group without keys (m = -inf)
-  l *= f;
+  for (int w = 1; w < kWavesA; ++w) mx = fmaxf(mx, red[w]);
+  for (int j = j0; j < n; j += kAttnThreads) score[j] = expf(score[j] - mx);
+  __syncthreads();
+  if (wave < kThreads / 64) {
+    float sum = 0.f;
+    for (int j = tid; j < n; j += kThreads) sum += score[j];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] *= f;
-#pragma unroll
-  for (int o = kChunks; o < 64; o <<= 1) {
-    l += __shfl_xor(l, o);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o);
+    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
+    if (lane == 0) red_sum[wave] = sum;
   }
-  if (lane < kChunks) {
+  float acc_o[4] = {0.f, 0.f, 0.f, 0.f};
+  auto add_value = [&](const uint2& v, float p) __attribute__((always_inline)) {
+    acc_o[0] = fmaf(p, bf16_to_f32(v.x & 0xffffu), acc_o[0]);
+    acc_o[1] = fmaf(p, bf16_to_f32(v.x >> 16), acc_o[1]);
+    acc_o[2] = fmaf(p, bf16_to_f32(v.y & 0xffffu), acc_o[2]);
+    acc_o[3] = fmaf(p, bf16_to_f32(v.y >> 16), acc_o[3]);
+  };
 #pragma unroll
-    for (int e = 0; e < 8; ++e) part[wave][8 * chunk + e] = acc[e];
-    if (lane == 0) red_l[wave] = l;
+  for (int u = 0; u < kVAhead; ++u) {
+    const int j = stripe + u * kStripes;
+    if (j < n) add_value(va[u], score[j]);
   }
+  for (int jb = stripe + kVAhead * kStripes; jb < n; jb += kVAhead * kStripes) {
+#pragma unroll
+    for (int u = 0; u < kVAhead; ++u)
+      if (jb + u * kStripes < n) va[u] = load_value(jb + u * kStripes);
+#pragma unroll
+    for (int u = 0; u < kVAhead; ++u)
+      if (jb + u * kStripes < n) add_value(va[u], score[jb + u * kStripes]);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[stripe][4 * quad + e] = acc_o[e];
   __syncthreads();
   if (tid < kDh) {
-    float o = 0.f, sum = 0.f;
+    float o = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWavesA; ++w) {
-      o += part[w][tid];
-      sum += red_l[w];
-    }
+    for (int st = 0; st < kStripes; ++st) o += part[st][tid];
+    const float sum = (red_sum[0] + red_sum[1]) + (red_sum[2] + red_sum[3]);
     out[(int64_t)t * d + h * kDh + tid] = (uint16_t)f32_to_bf16_rne(o / sum);
   }
 }

@@ -13,10 +13,10 @@ from tests.test_gpu_decoder import GpuDecoder, _check_logits, _model, _oracle_we
 pytestmark = pytest.mark.gpu
 
 
-# A round of keys is 6 * 1024 / (head_dim / 8): 768, 384 and 192 positions.
+# A round of keys is 512 positions; 20 values per stripe are 640, 320 and 160.
 @pytest.mark.parametrize("heads,head_dim,pos0,tokens", [
-    (4, 64, 0, 4), (4, 64, 769, 1), (4, 64, 127, 2), (2, 128, 0, 1), (2, 128, 1, 3),
-    (2, 128, 63, 1), (2, 128, 384, 4), (2, 128, 800, 1), (1, 256, 31, 2), (1, 256, 193, 4),
+    (4, 64, 0, 4), (4, 64, 1025, 1), (4, 64, 127, 2), (2, 128, 0, 1), (2, 128, 1, 3),
+    (2, 128, 63, 1), (2, 128, 318, 4), (2, 128, 513, 1), (1, 256, 31, 2), (1, 256, 159, 4),
     (17, 128, 70, 3)])
 def test_step_over_a_given_cache_matches_the_oracle(heads, head_dim, pos0, tokens):
     """Two layers, so the second layer's norm takes the experts' output."""

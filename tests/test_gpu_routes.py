@@ -4,7 +4,6 @@ from __future__ import annotations
 
 import numpy as np
 import pytest
-import torch
 
 import oracle as O
 from paper_2608_15383_amd import api
@@ -54,3 +53,26 @@ def test_layer_routing_equals_the_oracle(shape, tokens, given):
     assert np.array_equal(layer.ws_array("offsets", e + 1, np.int32), gr.offsets)
     assert np.array_equal(layer.ws_array("sorted_pairs", tokens * k, np.int32), gr.sorted_pairs)
     assert_close_rel(y, _y_ref(lay, r, k), f"{shape} T={tokens} given={given}")
+
+
+# More row tiles than co-resident workgroups: 200 experts (four rounds of the
+# lanes) with uneven rows, and one expert that takes every pair.
+@pytest.mark.parametrize("shape,tokens,skew", [
+    (LayerShape(512, 512, 200, 8), 3000, 1.2), (LayerShape(512, 512, 200, 8), 3001, 0.0),
+    (LayerShape(512, 512, 65, 4), 8200, 0.4), (LayerShape(256, 256, 1, 1), 33000, 0.0),
+    (LayerShape(256, 256, 2, 1), 33001, 3.0)])
+def test_many_row_tiles_match_the_gemv_path(shape, tokens, skew):
+    """Every row of the MFMA and mixed paths agrees with
+    the GEMV path, which has no row tiles."""
+    from paper_2608_15383_amd.inputs import zipf_gumbel_logits
+    lay = make_layer(shape, tokens, seed=8)
+    layer = Layer(dims_of(shape), lay, tokens)
+    rng = np.random.default_rng(9)
+    z = zipf_gumbel_logits(tokens, shape.n_experts, skew, rng.permutation(shape.n_experts), rng)
+    ref = layer.forward(lay.h, logits=z, path=api.EMOE_PATH_GEMV)
+    for path in (api.EMOE_PATH_MFMA, api.EMOE_PATH_MIXED):
+        y = layer.forward(lay.h, logits=z, path=path)
+        rms = np.sqrt((ref.astype(np.float64) ** 2).mean(axis=1))
+        err = np.sqrt(((y - ref).astype(np.float64) ** 2).mean(axis=1))
+        # bf16 pair outputs and sums in another order: about 2^-8 of a row.
+        assert (err <= 2e-2 * rms).all(), (path, int(np.argmax(err / rms)), float((err / rms).max()))
