@@ -96,7 +96,9 @@ __global__ __launch_bounds__(256) void quantize_kernel(int d, int f, int tiles_w
   constexpr uint32_t kMagicBits = 0x4B400000u;
   constexpr uint32_t kMagicSum = kMagicBits * 0x11111111u;  // sum over the eight shifts
   const float y = zero ? 0.f : 1.0f / s32;
-  const float s = zero ? 0.f : s32;
+  // An infinite maximum (a range error of the call) has y = 0; s = 0 keeps its
+  // finite weights' quotient 0.
+  const float s = zero || __builtin_isinf(s32) ? 0.f : s32;
   uint32_t out[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -108,7 +110,7 @@ __global__ __launch_bounds__(256) void quantize_kernel(int d, int f, int tiles_w
       const float quot = fmaf(fmaf(-q, s, v), y, q);
       dw += __float_as_uint(fmaxf(quot, -8.f) + kMagic) << (4 * (r >> 1) + 16 * (r & 1));
     }
-    out[i] = dw - kMagicSum;
+    out[i] = zero ? 0x88888888u : dw - kMagicSum;  // all 0, also in place of NaN
   }
   uint8_t* tile_ptr = rec + codes_off + ((int64_t)rb * G + g) * kTileBytes + 16 * lane;
   *reinterpret_cast<uint4*>(tile_ptr) = make_uint4(out[0], out[1], out[2], out[3]);

@@ -50,3 +50,48 @@ def test_gpu_codes_over_all_significands():
     assert np.array_equal(bf16_bits_to_f32(lay.w_gate).reshape(2048, 128), g)
     dm = dims_of(shape)
     _check_codes(dm, lay, quantize(dm, lay), [0])
+
+
+@pytest.mark.gpu
+def test_gpu_codes_of_groups_without_a_scale():
+    """A group whose scale is 0 (zeros, NaN, or a maximum below fp16's range)
+    has code 0 throughout, a NaN beside a scale the lowest code; beside an
+    infinite weight, which the call refuses, finite weights keep code 0."""
+    import torch
+    from paper_2608_15383_amd import api
+    from paper_2608_15383_amd.inputs import LayerShape, f32_to_bf16_bits, make_layer
+    from tests._gpu import dev, dims_of
+    shape = LayerShape(256, 128, 1, 1)
+    lay = make_layer(shape, 1, seed=2)
+    dm = dims_of(shape)
+
+    def codes(special):
+        """Codes of gate row 0, group 0: dword lane 16q + n of a tile holds row
+        n, inputs 32i + 8q + r at bits 4 (r / 2) + 16 (r % 2) of dword i."""
+        w = bf16_bits_to_f32(lay.w_gate).reshape(1, 128, 256).copy()
+        w[0, 0, :128] = special
+        bank = torch.zeros(api.expert_record_bytes(dm), dtype=torch.uint8, device="cuda")
+        err = False
+        try:
+            api.quantize_experts(dm, dev(f32_to_bf16_bits(w)), dev(lay.w_up), dev(lay.w_down), bank)
+        except Exception:
+            err = True
+        torch.cuda.synchronize()
+        dw = bank[:1024].cpu().numpy().view(np.uint32).reshape(64, 4)
+        j = np.arange(128)
+        i, q, r = j // 32, j % 32 // 8, j % 8
+        return (dw[16 * q, i] >> (4 * (r // 2) + 16 * (r % 2))) & 15, err
+
+    x = np.zeros(128, np.float32)
+    for fill in (0.0, np.nan, 2.0 ** -30):
+        x[:] = 0.0
+        x[::3] = fill
+        got, err = codes(x)
+        assert (got == 8).all() and not err, fill
+    x[:] = 1.0
+    x[5] = np.nan
+    got, err = codes(x)
+    assert got[5] == 0 and (np.delete(got, 5) == 15).all() and not err
+    x[5] = np.inf
+    got, err = codes(x)
+    assert got[5] == 0 and (np.delete(got, 5) == 8).all() and err
