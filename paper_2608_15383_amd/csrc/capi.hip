@@ -451,8 +451,8 @@ int32_t emoe_route(const emoe_dims* dims, int32_t T, const uint16_t* h, const ui
                 launch_router_logits(T, E, dims->d_model, h, w_router, logits, stream));
   if (T > 0)
     EMOE_LAUNCH(EMOE_K_TOPK, stream,
-              launch_topk(T, E, k, renormalize, LogitSource{z, nullptr, nullptr, 0}, topk_ids, topk_w,
-                          stream));
+                launch_topk(T, E, k, renormalize, LogitSource{z, nullptr, nullptr, 0}, topk_ids,
+                            topk_w, stream));
   EMOE_LAUNCH(EMOE_K_GROUP, stream,
               launch_group(T * k, E, topk_ids, counts, offsets, sorted_pairs, active, n_active,
                            nullptr, nullptr, 1, stream));
@@ -841,10 +841,11 @@ int32_t forward_impl(emoe_cache* c, int32_t T, const uint16_t* h, const uint16_t
   // Route (Eq. 1) and group by expert.  On the MFMA path the router also sums
   // each token row's input groups (the accumulator starts of the gate/up MFMA
   // chains) when d is a multiple of 512; otherwise extra workgroups of the
-  // top-k launch form them (a launch of their own took 2 to 5 us).  A small call's router leaves the logits as sums
-  // over slices of d, in the pair-output array, which only the down projection
-  // writes (k * d floats per token hold E doubles per slice: a slice is at
-  // least 512 inputs, and E at most 256).
+  // top-k launch form them (a launch of their own took 2 to 5 us).  A small
+  // call's router leaves the logits as sums over slices of d, in the
+  // pair-output array, which only the down projection writes (k * d floats per
+  // token hold E doubles per slice: a slice is at least 512 inputs, and E at
+  // most 256).
   float* tok_bias = reinterpret_cast<float*>(ws + L.tok_bias);
   const bool uses_mfma = path != EMOE_PATH_GEMV;
   const bool fused_bias = uses_mfma && !logits_override && d % 512 == 0;
