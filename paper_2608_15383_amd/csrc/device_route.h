@@ -380,10 +380,12 @@ __device__ __forceinline__ int wave_exclusive_scan(int v, int& total) {
 }
 
 // LDS of the block-wide grouping: per wavefront and expert, first the
-// wavefront's count, then its first grouped position.
+// wavefront's count, then its first grouped position; and the sums (pairs,
+// active experts, row tiles) of each block of 64 experts.
 template <int kThreads>
 struct GroupShared {
   int wbase[kThreads / 64][EMOE_MAX_EXPERTS];
+  int block_sum[kPerLane][3];
 };
 
 // Lanes of the wavefront whose expert equals this lane's (valid lanes only),
@@ -455,44 +457,55 @@ __device__ __forceinline__ void block_group(
   __syncthreads();
 
   // Totals, offsets, active list, row tiles; then each wavefront's base.
-  // Lane l takes experts l, 64 + l, ..: one round of LDS reads and one scan
-  // for up to 64 experts, the carries running over the rounds (four
-  // neighbouring experts a lane, kWaves reads in a chain each, took 1.1 us
-  // more at 64 experts).
-  if (wave == 0) {
-    int base = 0, nz_base = 0, tl_base = 0;
-    for (int e0 = 0; e0 < n_experts; e0 += 64) {
-      const int e = e0 + lane;
-      const bool ok = e < n_experts;
-      int own[kWaves], c = 0;
+  // Wavefront b scans experts 64b + lane, one round of LDS reads; above 64
+  // experts the blocks' sums meet through LDS.  The chain of a block is the
+  // whole cost: four neighbouring experts a lane on one wavefront took 1.1 us
+  // more at 64 experts, the blocks one after the other on one wavefront 1.6 us
+  // more at 256.
+  static_assert(kWaves >= kPerLane, "a wavefront per block of 64 experts");
+  const int blocks = (n_experts + 63) / 64;
+  const int e = 64 * wave + lane;
+  const bool ok = e < n_experts;
+  int own[kWaves], c = 0, at = 0, nz_at = 0, tl_at = 0;
+  int total = 0, nz_total = 0, tl_total = 0;
+  if (wave < blocks) {
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) own[w] = ok ? sh.wbase[w][e] : 0;
+    for (int w = 0; w < kWaves; ++w) own[w] = ok ? sh.wbase[w][e] : 0;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) c += own[w];
-      int total, nz_total, tl_total;
-      const int at = base + wave_exclusive_scan(c, total);
-      const int nz_at = nz_base + wave_exclusive_scan(c > 0, nz_total);
-      const int tl_at = tl_base + wave_exclusive_scan(mfma_row_tiles(c, mfma_rows), tl_total);
-      if (ok) {
-        st_u32<kCo>(counts + e, (uint32_t)c);
-        st_u32<kCo>(offsets + e, (uint32_t)at);
-        if (tile_offsets) st_u32<kCo>(tile_offsets + e, (uint32_t)tl_at);
-        if (c > 0) st_u32<kCo>(active + nz_at, (uint32_t)e);
-        int run = at;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-          sh.wbase[w][e] = run;
-          run += own[w];
-        }
-      }
-      base += total;
-      nz_base += nz_total;
-      tl_base += tl_total;
+    for (int w = 0; w < kWaves; ++w) c += own[w];
+    at = wave_exclusive_scan(c, total);
+    nz_at = wave_exclusive_scan(c > 0, nz_total);
+    tl_at = wave_exclusive_scan(mfma_row_tiles(c, mfma_rows), tl_total);
+    if (blocks > 1 && lane == 0) {
+      sh.block_sum[wave][0] = total;
+      sh.block_sum[wave][1] = nz_total;
+      sh.block_sum[wave][2] = tl_total;
     }
-    if (lane == 0) {
-      st_u32<kCo>(offsets + n_experts, (uint32_t)base);
-      if (tile_offsets) st_u32<kCo>(tile_offsets + n_experts, (uint32_t)tl_base);
-      st_u32<kCo>(n_active, (uint32_t)nz_base);
+  }
+  if (blocks > 1) __syncthreads();
+  if (wave < blocks) {
+    int base = 0, nz_base = 0, tl_base = 0;
+    for (int b = 0; b < wave; ++b) {
+      base += sh.block_sum[b][0];
+      nz_base += sh.block_sum[b][1];
+      tl_base += sh.block_sum[b][2];
+    }
+    if (ok) {
+      st_u32<kCo>(counts + e, (uint32_t)c);
+      st_u32<kCo>(offsets + e, (uint32_t)(base + at));
+      if (tile_offsets) st_u32<kCo>(tile_offsets + e, (uint32_t)(tl_base + tl_at));
+      if (c > 0) st_u32<kCo>(active + nz_base + nz_at, (uint32_t)e);
+      int run = base + at;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        sh.wbase[w][e] = run;
+        run += own[w];
+      }
+    }
+    if (wave == blocks - 1 && lane == 0) {
+      st_u32<kCo>(offsets + n_experts, (uint32_t)(base + total));
+      if (tile_offsets) st_u32<kCo>(tile_offsets + n_experts, (uint32_t)(tl_base + tl_total));
+      st_u32<kCo>(n_active, (uint32_t)(nz_base + nz_total));
     }
   }
   __syncthreads();

@@ -12,6 +12,8 @@
 //   group_kernel:         per-expert counts, exclusive offsets, a stable
 //                         counting sort of pair ids, the ascending active list
 //                         and (optionally) the MFMA row-tile prefix sum.
+#include <type_traits>
+
 #include "device_route.h"
 
 namespace emoe {
@@ -320,6 +322,7 @@ __global__ __launch_bounds__(64 * kChunkWaves) void chunk_place_kernel(
   __shared__ int part_pre[kChunkWaves][EMOE_MAX_EXPERTS];
   // Wavefront w's chunk: its count per expert, then its first position.
   __shared__ int base[kChunkWaves][EMOE_MAX_EXPERTS];
+  __shared__ int block_sum[kPerLane][3];  // pairs, active experts, tiles per 64 experts
   const int lane = lane_id();
   const int wave = threadIdx.x >> 6;
   const int n_chunks = (pairs + 63) / 64;
@@ -328,71 +331,95 @@ __global__ __launch_bounds__(64 * kChunkWaves) void chunk_place_kernel(
   // Bound by its chain of latencies (one round of loads, the scan, the
   // placement): the scan as four strided experts a lane, with its chunks'
   // counts read from memory there, made it 8.7 us at 2048 tokens, now 6.4.
+  // 16 loads in flight: 16 chunks of the one block of up to 64 experts, or
+  // four chunks of each of the four blocks.  With the blocks one after the
+  // other here and in the scan, 256 experts and 32 chunks took 10.1 us; now 5.1.
+  auto sum_chunks = [&](auto blocks_c) __attribute__((always_inline)) {
+    constexpr int kQ = decltype(blocks_c)::value;
+    constexpr int kBatch = 16 / kQ;
+    int all[kQ], pre[kQ], mine[kQ];  // mine: chunk c0 + wave, one of the wavefront's own
 #pragma unroll
-  for (int q = 0; q < kPerLane; ++q) {
-    const int e = 64 * q + lane;
-    if (e >= n_experts) break;
-    base[wave][e] = c0 + wave < n_chunks ? chunk_counts[(int64_t)(c0 + wave) * n_experts + e] : 0;
-    int all = 0, pre = 0;
-    // Loads in batches of 16, so one memory latency covers 16 chunks.
-    constexpr int kBatch = 16;
+    for (int q = 0; q < kQ; ++q) all[q] = pre[q] = mine[q] = 0;
     for (int cb = wave; cb < n_chunks; cb += kBatch * kChunkWaves) {
-      int v[kBatch];
+      int v[kBatch][kQ];
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const int c = cb + j * kChunkWaves;
-        v[j] = c < n_chunks ? chunk_counts[(int64_t)c * n_experts + e] : 0;
-      }
+      for (int j = 0; j < kBatch; ++j)
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        all += v[j];
-        if (cb + j * kChunkWaves < c0) pre += v[j];
-      }
+        for (int q = 0; q < kQ; ++q) {
+          const int c = cb + j * kChunkWaves, e = 64 * q + lane;
+          v[j][q] = c < n_chunks && e < n_experts ? chunk_counts[(int64_t)c * n_experts + e] : 0;
+        }
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j)
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+          all[q] += v[j][q];
+          if (cb + j * kChunkWaves < c0) pre[q] += v[j][q];
+          if (cb + j * kChunkWaves == c0 + wave) mine[q] = v[j][q];
+        }
     }
-    part_all[wave][e] = all;
-    part_pre[wave][e] = pre;
-  }
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      part_all[wave][64 * q + lane] = all[q];
+      part_pre[wave][64 * q + lane] = pre[q];
+      base[wave][64 * q + lane] = mine[q];
+    }
+  };
+  if (n_experts <= 64)
+    sum_chunks(std::integral_constant<int, 1>());
+  else
+    sum_chunks(std::integral_constant<int, kPerLane>());
   __syncthreads();
-  if (wave == 0) {
-    // Lane l takes experts l, 64 + l, ..: one round for up to 64 experts.
-    int off0 = 0, nz0 = 0, tl0 = 0;
+  // Wavefront b scans experts 64b + lane; above 64 experts the blocks' sums
+  // meet through LDS.
+  const int blocks = (n_experts + 63) / 64;
+  const int x = 64 * wave + lane;
+  const bool ok = x < n_experts;
+  int own[kChunkWaves], cnt = 0, pre = 0, off = 0, nz = 0, tl = 0;
+  int total = 0, nz_total = 0, tl_total = 0;
+  if (wave < blocks) {
+#pragma unroll
+    for (int w = 0; w < kChunkWaves; ++w) {
+      own[w] = ok ? base[w][x] : 0;
+      cnt += ok ? part_all[w][x] : 0;
+      pre += ok ? part_pre[w][x] : 0;
+    }
+    off = wave_exclusive_scan(cnt, total);
+    nz = wave_exclusive_scan(cnt > 0, nz_total);
+    tl = wave_exclusive_scan(mfma_row_tiles(cnt, mfma_rows), tl_total);
+    if (blocks > 1 && lane == 0) {
+      block_sum[wave][0] = total;
+      block_sum[wave][1] = nz_total;
+      block_sum[wave][2] = tl_total;
+    }
+  }
+  if (blocks > 1) __syncthreads();
+  if (wave < blocks) {
     const bool writer = blockIdx.x == 0;
-    for (int e0 = 0; e0 < n_experts; e0 += 64) {
-      const int e = e0 + lane;
-      const bool ok = e < n_experts;
-      int own[kChunkWaves], cnt = 0, pre = 0;
+    int off0 = 0, nz0 = 0, tl0 = 0;
+    for (int b = 0; b < wave; ++b) {
+      off0 += block_sum[b][0];
+      nz0 += block_sum[b][1];
+      tl0 += block_sum[b][2];
+    }
+    if (ok) {
+      if (writer) {
+        counts[x] = cnt;
+        offsets[x] = off0 + off;
+        tile_offsets[x] = tl0 + tl;
+        if (cnt > 0) active[nz0 + nz] = x;
+      }
+      int run = off0 + off + pre;
 #pragma unroll
       for (int w = 0; w < kChunkWaves; ++w) {
-        own[w] = ok ? base[w][e] : 0;
-        cnt += ok ? part_all[w][e] : 0;
-        pre += ok ? part_pre[w][e] : 0;
+        base[w][x] = run;
+        run += own[w];
       }
-      int total, nz_total, tl_total;
-      const int off = off0 + wave_exclusive_scan(cnt, total);
-      const int nz = nz0 + wave_exclusive_scan(cnt > 0, nz_total);
-      const int tl = tl0 + wave_exclusive_scan(mfma_row_tiles(cnt, mfma_rows), tl_total);
-      if (ok) {
-        if (writer) {
-          counts[e] = cnt;
-          offsets[e] = off;
-          tile_offsets[e] = tl;
-          if (cnt > 0) active[nz] = e;
-        }
-        int run = off + pre;
-#pragma unroll
-        for (int w = 0; w < kChunkWaves; ++w) {
-          base[w][e] = run;
-          run += own[w];
-        }
-      }
-      off0 += total;
-      nz0 += nz_total;
-      tl0 += tl_total;
     }
-    if (writer && lane == 0) {
-      offsets[n_experts] = off0;
-      tile_offsets[n_experts] = tl0;
-      *n_active = nz0;
+    if (writer && wave == blocks - 1 && lane == 0) {
+      offsets[n_experts] = off0 + total;
+      tile_offsets[n_experts] = tl0 + tl_total;
+      *n_active = nz0 + nz_total;
     }
   }
   __syncthreads();

@@ -4,12 +4,13 @@ from __future__ import annotations
 
 import numpy as np
 import pytest
+import torch
 
 import oracle as O
 from paper_2608_15383_amd import api
 from paper_2608_15383_amd.inputs import LayerShape, bf16_bits_to_f32, make_layer
 
-from _gpu import Layer, assert_close_rel, dims_of
+from _gpu import Layer, assert_close_rel, dev, dims_of
 
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +77,43 @@ def test_many_row_tiles_match_the_gemv_path(shape, tokens, skew):
         err = np.sqrt(((y - ref).astype(np.float64) ** 2).mean(axis=1))
         # bf16 pair outputs and sums in another order: about 2^-8 of a row.
         assert (err <= 2e-2 * rms).all(), (path, int(np.argmax(err / rms)), float((err / rms).max()))
+
+
+# Experts on both sides of the scans' blocks of 64; pairs on both sides of the
+# one-workgroup grouping (1024) and of a pass over the chunk counts (64 chunks
+# above 64 experts, 256 below); k = 5 takes the counts' own launch.
+@pytest.mark.parametrize("experts", [64, 65, 128, 129, 192, 193, 256])
+@pytest.mark.parametrize("tokens,k", [(1, 8), (128, 8), (129, 8), (207, 5), (512, 8), (513, 8),
+                                      (2100, 8), (64, 17)])
+def test_grouping_over_blocks_of_experts_equals_the_oracle(experts, tokens, k):
+    """Every array of the grouping, in a layer call and in emoe_route; a third
+    of the experts never chosen, so the active list has gaps in every block."""
+    shape = LayerShape(128, 128, experts, k)
+    lay = make_layer(shape, tokens, seed=17)
+    layer = Layer(dims_of(shape), lay, tokens)
+    rng = np.random.default_rng([experts, tokens])
+    z = rng.standard_normal((tokens, experts)).astype(np.float32)
+    z[:, ::3] -= 50
+    layer.ws.fill_(0xA5)
+    layer.forward(lay.h, logits=z, path=api.EMOE_PATH_MFMA)
+    pairs = tokens * k
+    ids = O.topk_experts(z, k)
+    gr = O.group_by_expert(ids, experts)
+    tiles = np.concatenate([[0], np.cumsum((gr.counts + 63) // 64)]).astype(np.int32)
+    pos = np.empty(pairs, np.int32)
+    pos[gr.sorted_pairs] = np.arange(pairs, dtype=np.int32)
+    want = dict(topk_ids=ids.reshape(-1), counts=gr.counts, offsets=gr.offsets,
+                sorted_pairs=gr.sorted_pairs, active=gr.active, n_active=[len(gr.active)],
+                tile_offsets=tiles, pair_pos=pos)
+    for name, w in want.items():
+        got = layer.ws_array(name, len(w), np.int32)
+        assert np.array_equal(got, np.asarray(w, np.int32)), name
+    i32 = lambda n: torch.full((n,), -1, dtype=torch.int32, device="cuda:0")
+    out = dict(topk_ids=i32(pairs), counts=i32(experts), offsets=i32(experts + 1),
+               sorted_pairs=i32(pairs), active=i32(experts), n_active=i32(1))
+    api.route(layer.dm, tokens, dev(lay.h), layer.wr, dev(z), True, None, out["topk_ids"],
+              torch.empty(pairs, device="cuda:0"), out["counts"], out["offsets"],
+              out["sorted_pairs"], out["active"], out["n_active"])
+    for name, t in out.items():
+        w = np.asarray(want[name], np.int32)
+        assert np.array_equal(t.cpu().numpy()[:len(w)], w), name
