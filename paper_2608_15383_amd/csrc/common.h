@@ -279,11 +279,13 @@ struct LogitSource {
 };
 
 // Row sums riding along with a top-k launch (x null: none): bias[t][g] = -136
-// * the sum of the 128-input group g of row t of x [tokens][d], fp32.
+// * the sum of the 128-input group g of row t of x [tokens][d], fp32, by the
+// workgroups from `first` on (set by the launch).
 struct RowBias {
   const uint16_t* x = nullptr;
   float* bias = nullptr;
   int32_t d = 0;
+  int32_t first = 0;
 };
 
 // Slices of d over which launch_router_logits should split a call (1: none).
@@ -298,10 +300,10 @@ hipError_t launch_router_logits(int tokens, int n_experts, int d, const uint16_t
 
 hipError_t launch_topk(int tokens, int n_experts, int top_k, int renormalize,
                        const LogitSource& src, int32_t* topk_ids, float* topk_w, hipStream_t stream,
-                       const RowBias& rb = RowBias());
+                       RowBias rb = RowBias());
 
 // The row sums as a launch of their own.
-hipError_t launch_row_bias(int tokens, const RowBias& rb, hipStream_t stream);
+hipError_t launch_row_bias(int tokens, RowBias rb, hipStream_t stream);
 
 // launch_topk and launch_group in one launch, for calls of at most
 // kTopkGroupMaxTokens tokens.
@@ -311,7 +313,7 @@ hipError_t launch_topk_group(int tokens, int n_experts, int top_k, int renormali
                              int32_t* counts, int32_t* offsets, int32_t* sorted_pairs,
                              int32_t* active, int32_t* n_active, int32_t* tile_offsets,
                              int32_t* pair_pos, int mfma_rows, hipStream_t stream,
-                             const RowBias& rb = RowBias());
+                             RowBias rb = RowBias());
 
 // Grouping by expert (Sec. 3.4 step 1) in one workgroup; pair_pos receives
 // the inverse permutation (grouped position of each pair id), tile_offsets
@@ -332,7 +334,7 @@ constexpr bool topk_count_fits(int top_k) { return top_k >= 4 && 64 % top_k == 0
 hipError_t launch_topk_count(int tokens, int n_experts, int top_k, int renormalize,
                              const LogitSource& src, int32_t* topk_ids, float* topk_w,
                              int32_t* chunk_counts, hipStream_t stream,
-                             const RowBias& rb = RowBias());
+                             RowBias rb = RowBias());
 hipError_t launch_group_place(int pairs, int n_experts, const int32_t* topk_ids,
                               const int32_t* chunk_counts, int32_t* counts, int32_t* offsets,
                               int32_t* sorted_pairs, int32_t* active, int32_t* n_active,

@@ -118,20 +118,21 @@ __global__ __launch_bounds__(256) void router_logits_kernel(int tokens, int n_ex
 
 // Selection from token t's logits: as given, or (src.slices > 0) the router's
 // slice sums added in order and rounded to fp32, which are then also stored
-// as the call's logits.
+// as the call's logits.  One selection after either source: a copy of it per
+// source made the top-k launches 0.2 to 0.6 us longer.
 __device__ __forceinline__ void topk_select_from(const LogitSource& src, int t, int tokens,
                                                  int n_experts, int top_k, TopkState& st,
                                                  uint64_t* scratch) {
-  if (src.slices == 0) {
-    wave_topk_select<false>(src.logits + (int64_t)t * n_experts, n_experts, top_k, st, scratch);
-    return;
-  }
   const int lane = lane_id();
 #pragma unroll
   for (int c = 0; c < kPerLane; ++c) {
     const int e = lane + 64 * c;
     st.v[c] = 0.f;
     if (e >= n_experts) continue;
+    if (src.slices == 0) {
+      st.v[c] = src.logits[(int64_t)t * n_experts + e];
+      continue;
+    }
     const double* p = src.parts + (int64_t)t * n_experts + e;
     double v[kRouterMaxSlices];
 #pragma unroll
@@ -174,17 +175,17 @@ __device__ __forceinline__ void wave_row_bias(int t, int K, const uint16_t* __re
   }
 }
 
-// Workgroups from `first` on form the row biases, one token per wavefront:
+// Workgroups from rb.first on form the row biases, one token per wavefront:
 // they ride along with the top-k launch, which saves one of their own.
-__device__ __forceinline__ bool row_bias_block(const RowBias& rb, int first, int tokens) {
-  if ((int)blockIdx.x < first) return false;
-  const int t = ((int)blockIdx.x - first) * (blockDim.x >> 6) + (threadIdx.x >> 6);
+__device__ __forceinline__ bool row_bias_block(const RowBias& rb, int tokens) {
+  if ((int)blockIdx.x < rb.first) return false;
+  const int t = ((int)blockIdx.x - rb.first) * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (t < tokens) wave_row_bias(t, rb.d, rb.x, rb.bias);
   return true;
 }
 
 __global__ __launch_bounds__(256) void row_bias_kernel(int tokens, RowBias rb) {
-  row_bias_block(rb, 0, tokens);
+  row_bias_block(rb, tokens);
 }
 
 __global__ __launch_bounds__(256) void topk_kernel(int tokens, int n_experts, int top_k,
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(256) void topk_kernel(int tokens, int n_experts, in
                                                    int32_t* __restrict__ topk_ids,
                                                    float* __restrict__ topk_w, RowBias rb) {
   __shared__ uint64_t s_rank[4][64];  // per-wavefront top-k scratch
-  if (row_bias_block(rb, (tokens + 3) / 4, tokens)) return;
+  if (row_bias_block(rb, tokens)) return;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= tokens) return;
   TopkState st;
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(1024) void topk_count_kernel(int tokens, int n_expe
   __shared__ int s_pair[64];           // the chunk's expert ids, pair order
   __shared__ int row[EMOE_MAX_EXPERTS];
   const int per = 64 / top_k;
-  if (row_bias_block(rb, (tokens + per - 1) / per, tokens)) return;
+  if (row_bias_block(rb, tokens)) return;
   const int lane = lane_id();
   const int wave = threadIdx.x >> 6;
   const int c = blockIdx.x;
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(
     int32_t* __restrict__ pair_pos, int mfma_rows, RowBias rb) {
   __shared__ uint64_t s_rank[kGroupThreads / 64][64];
   __shared__ GroupShared<kGroupThreads> sh;
-  if (row_bias_block(rb, 1, tokens)) return;
+  if (row_bias_block(rb, tokens)) return;
   const int wave = threadIdx.x >> 6;
   for (int t = wave; t < tokens; t += kGroupThreads / 64) {
     TopkState st;
@@ -485,35 +486,40 @@ hipError_t launch_router_logits(int tokens, int n_experts, int d, const uint16_t
 }
 
 namespace {
-inline int bias_blocks(const RowBias& rb, int tokens, int waves) {
-  return rb.x ? (tokens + waves - 1) / waves : 0;
+// Grid of a launch of `blocks` workgroups of `waves` wavefronts with the row
+// biases' workgroups after them.
+inline dim3 bias_grid(RowBias& rb, int blocks, int tokens, int waves) {
+  rb.first = blocks;
+  return dim3(blocks + (rb.x ? (tokens + waves - 1) / waves : 0));
 }
 }  // namespace
 
-hipError_t launch_row_bias(int tokens, const RowBias& rb, hipStream_t stream) {
+hipError_t launch_row_bias(int tokens, RowBias rb, hipStream_t stream) {
   if (tokens == 0) return hipSuccess;
-  launch(row_bias_kernel, dim3(bias_blocks(rb, tokens, 4)), dim3(256), stream, tokens, rb);
+  const dim3 grid = bias_grid(rb, 0, tokens, 4);
+  launch(row_bias_kernel, grid, dim3(256), stream, tokens, rb);
   return hipGetLastError();
 }
 
 hipError_t launch_topk(int tokens, int n_experts, int top_k, int renormalize,
                        const LogitSource& src, int32_t* topk_ids, float* topk_w, hipStream_t stream,
-                       const RowBias& rb) {
+                       RowBias rb) {
   if (tokens == 0) return hipSuccess;
-  launch(topk_kernel, dim3((tokens + 3) / 4 + bias_blocks(rb, tokens, 4)), dim3(256), stream, tokens,
-         n_experts, top_k, renormalize, src, topk_ids, topk_w, rb);
+  const dim3 grid = bias_grid(rb, (tokens + 3) / 4, tokens, 4);
+  launch(topk_kernel, grid, dim3(256), stream, tokens, n_experts, top_k, renormalize, src, topk_ids,
+         topk_w, rb);
   return hipGetLastError();
 }
 
 hipError_t launch_topk_count(int tokens, int n_experts, int top_k, int renormalize,
                              const LogitSource& src, int32_t* topk_ids, float* topk_w,
-                             int32_t* chunk_counts, hipStream_t stream, const RowBias& rb) {
+                             int32_t* chunk_counts, hipStream_t stream, RowBias rb) {
   if (tokens == 0) return hipSuccess;
   if (top_k < 1 || 64 % top_k != 0 || 64 / top_k > 16) return hipErrorInvalidValue;
   const int per = 64 / top_k;  // tokens (wavefronts) per chunk
-  launch(topk_count_kernel, dim3((tokens + per - 1) / per + bias_blocks(rb, tokens, per)),
-         dim3(64 * per), stream, tokens, n_experts, top_k, renormalize, src, topk_ids, topk_w,
-         chunk_counts, rb);
+  const dim3 grid = bias_grid(rb, (tokens + per - 1) / per, tokens, per);
+  launch(topk_count_kernel, grid, dim3(64 * per), stream, tokens, n_experts, top_k, renormalize, src,
+         topk_ids, topk_w, chunk_counts, rb);
   return hipGetLastError();
 }
 
@@ -522,11 +528,12 @@ hipError_t launch_topk_group(int tokens, int n_experts, int top_k, int renormali
                              int32_t* counts, int32_t* offsets, int32_t* sorted_pairs,
                              int32_t* active, int32_t* n_active, int32_t* tile_offsets,
                              int32_t* pair_pos, int mfma_rows, hipStream_t stream,
-                             const RowBias& rb) {
+                             RowBias rb) {
   if (tokens == 0) return hipSuccess;
-  launch(topk_group_kernel, dim3(1 + bias_blocks(rb, tokens, kGroupThreads / 64)),
-         dim3(kGroupThreads), stream, tokens, n_experts, top_k, renormalize, src, topk_ids, topk_w,
-         counts, offsets, sorted_pairs, active, n_active, tile_offsets, pair_pos, mfma_rows, rb);
+  const dim3 grid = bias_grid(rb, 1, tokens, kGroupThreads / 64);
+  launch(topk_group_kernel, grid, dim3(kGroupThreads), stream, tokens, n_experts, top_k, renormalize,
+         src, topk_ids, topk_w, counts, offsets, sorted_pairs, active, n_active, tile_offsets, pair_pos,
+         mfma_rows, rb);
   return hipGetLastError();
 }
 
