@@ -869,12 +869,13 @@ int32_t forward_impl(emoe_cache* c, int32_t T, const uint16_t* h, const uint16_t
     rb.d = d;
   }
   if (rb.x && path == EMOE_PATH_MIXED) {
-    // The mixed path (asked for by name) reports them as a kernel of their own.
+    // The mixed path runs only when asked for by name and keeps the launches
+    // that its callers count: the row sums apart, top-k and grouping apart.
     EMOE_LAUNCH(EMOE_K_ROW_BIAS, stream, launch_row_bias(T, rb, stream));
     ds.kernel_launches += 1;
     rb = RowBias();
   }
-  if (T <= kTopkGroupMaxTokens && P <= kGroupWideMinPairs && path != EMOE_PATH_MIXED) {
+  if (topk_group_fits(T, E) && path != EMOE_PATH_MIXED) {
     EMOE_LAUNCH(EMOE_K_TOPK, stream,
                 launch_topk_group(T, E, k, renormalize, src, ids, wts, counts, offsets, sorted,
                                   active, n_active, tiles, pair_pos, mfma_rows, stream, rb));

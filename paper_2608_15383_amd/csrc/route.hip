@@ -258,10 +258,9 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(
 }
 
 // Top-k and grouping of a small call in one launch: workgroup 0's 16
-// wavefronts take the tokens in turn, then group all pairs.  Bound by latency:
-// each token costs its wavefront about 0.7 us, so kTopkGroupMaxTokens
-// sends few tokens per wavefront here; the separate launches cost
-// their start, their gap and a round trip of the ids.
+// wavefronts take the tokens in turn, then group all pairs.  It saves a
+// launch's start, its gap and a round trip of the ids, and pays for a top-k
+// of all tokens on one CU, so only calls that topk_group_fits admits take it.
 __global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(
     int tokens, int n_experts, int top_k, int renormalize, LogitSource src,
     int32_t* __restrict__ topk_ids, float* __restrict__ topk_w, int32_t* __restrict__ counts,

@@ -23,14 +23,17 @@ def _y_ref(lay, r, k):
 
 
 # One, two and four slices of d and none (d not a multiple of 512); tokens on
-# both sides of the fused top-k and grouping (64) and of the wide grouping
-# (1024 pairs), with k dividing 64 or not; a partial token and expert tile.
+# both sides of the fused top-k and grouping (12, and 64 experts) and of the
+# wide grouping (1024 pairs), with k dividing 64 or not; a partial token and
+# expert tile.
 @pytest.mark.parametrize("shape,tokens", [
     (LayerShape(512, 128, 6, 2), 5), (LayerShape(1024, 128, 17, 3), 16),
     (LayerShape(2048, 128, 64, 8), 17), (LayerShape(2048, 128, 200, 8), 64),
     (LayerShape(1024, 128, 64, 8), 65), (LayerShape(640, 128, 12, 3), 64),
     (LayerShape(640, 128, 12, 3), 343), (LayerShape(384, 128, 16, 8), 130),
-    (LayerShape(2048, 128, 16, 8), 129)])
+    (LayerShape(2048, 128, 16, 8), 129), (LayerShape(1024, 128, 64, 8), 12),
+    (LayerShape(1024, 128, 64, 64), 12), (LayerShape(640, 128, 64, 8), 13),
+    (LayerShape(1024, 128, 65, 8), 12)])
 @pytest.mark.parametrize("given", [False, True])
 def test_layer_routing_equals_the_oracle(shape, tokens, given):
     """Logits, ids, weights and grouping of a layer call on the MFMA path, and
@@ -54,6 +57,18 @@ def test_layer_routing_equals_the_oracle(shape, tokens, given):
     assert np.array_equal(layer.ws_array("offsets", e + 1, np.int32), gr.offsets)
     assert np.array_equal(layer.ws_array("sorted_pairs", tokens * k, np.int32), gr.sorted_pairs)
     assert_close_rel(y, _y_ref(lay, r, k), f"{shape} T={tokens} given={given}")
+
+
+@pytest.mark.parametrize("experts,tokens,launches", [
+    (64, 5, 5), (64, 12, 5), (64, 13, 6), (64, 64, 6), (65, 12, 6), (200, 5, 6), (8, 12, 5), (8, 16, 6)])
+def test_one_routing_launch_only_for_the_smallest_calls(experts, tokens, launches):
+    """Above 12 tokens or 64 experts the top-k keeps its own launch: all tokens
+    on one compute unit cost more there than the launch saved."""
+    shape = LayerShape(512, 128, experts, 4)
+    lay = make_layer(shape, tokens, seed=5)
+    st = api.Stats()
+    Layer(dims_of(shape), lay, tokens).forward(lay.h, stats=st)
+    assert st.kernel_launches == launches  # router, routing (1 or 2), gate/up, down, combine
 
 
 # More row tiles than co-resident workgroups: 200 experts (four rounds of the
