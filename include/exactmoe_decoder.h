@@ -91,6 +91,12 @@ int32_t emoe_decoder_forward(emoe_decoder* dec, const int32_t* tokens, int32_t T
                              float* logits, int32_t* next_token, void* workspace,
                              size_t workspace_bytes, hipStream_t stream, emoe_stats* stats);
 
+/* Test hook: decode steps (T <= 4) whose last position is below `keys` take
+ * the one-launch rotation and attention, longer ones the two launches of
+ * prompts; both give the same bits.  0 .. EMOE_DECODER_MAX_POSITIONS; -1
+ * restores the default, which depends on the head size. */
+int32_t emoe_test_set_step_keys(emoe_decoder* dec, int32_t keys);
+
 #ifdef __cplusplus
 }
 #endif

@@ -98,6 +98,7 @@ SIGNATURES = {
     "emoe_decoder_create": (_i32, [C.POINTER(DecoderDims), C.POINTER(DecoderWeights),
                                    C.POINTER(_vp), _vp, C.POINTER(_vp)]),
     "emoe_decoder_destroy": (_i32, [_vp]),
+    "emoe_test_set_step_keys": (_i32, [_vp, _i32]),
     "emoe_decoder_forward": (_i32, [_vp, _vp, _i32, _i32, _vp, _vp, _vp, C.c_size_t, _vp,
                                     C.POINTER(Stats)]),
     "emoe_profile_begin": (_i32, [_i32]),

@@ -251,6 +251,11 @@ class Decoder:
         except Exception:
             pass
 
+    def set_step_keys(self, keys: int = -1) -> None:
+        """emoe_test_set_step_keys: positions up to which a decode step runs rotation and
+        attention in one launch (test hook; -1 restores the default)."""
+        check(lib().emoe_test_set_step_keys(self.handle, int(keys)))
+
     def forward(self, tokens, pos0: int, logits, next_token, workspace, stream=None,
                 stats: Stats | None = None) -> None:
         """emoe_decoder_forward: tokens (device int32 [T]) at positions pos0 .. pos0+T-1."""

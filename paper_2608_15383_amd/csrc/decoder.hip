@@ -311,6 +311,14 @@ __device__ __forceinline__ void rope_cos_sin(double x, float& c, float& s) {
   s = (float)(k >= 2 ? -b : b);
 }
 
+// Rotation of the pair (a, b) by the angle of cosine c and sine s, with the
+// roundings spelled out: the prompt's and the step's kernels share them.
+__device__ __forceinline__ void rope_pair(float a, float b, float c, float s, uint16_t& ra,
+                                          uint16_t& rb) {
+  ra = (uint16_t)f32_to_bf16_rne(fmaf(a, c, -(b * s)));
+  rb = (uint16_t)f32_to_bf16_rne(fmaf(a, s, b * c));
+}
+
 // Rotary positions on q (in place in qkv) and k, and the cache append of k
 // and v, for token t at position pos0 + t.  Element i < Dh/2 of a head pairs
 // with i + Dh/2; the angle p * base^(-2i/Dh) and its sine and cosine are
@@ -336,12 +344,8 @@ __global__ __launch_bounds__(kThreads) void rope_kv_kernel(int H, int Dh, int po
     const int h = j / half, i = j % half;
     const float c = cs[i][0], s = cs[i][1];
     const int a = h * Dh + i, b = a + half;
-    const float qa = bf16_to_f32(q[a]), qb = bf16_to_f32(q[b]);
-    q[a] = (uint16_t)f32_to_bf16_rne(qa * c - qb * s);
-    q[b] = (uint16_t)f32_to_bf16_rne(qb * c + qa * s);
-    const float ka = bf16_to_f32(k[a]), kb = bf16_to_f32(k[b]);
-    kc[a] = (uint16_t)f32_to_bf16_rne(ka * c - kb * s);
-    kc[b] = (uint16_t)f32_to_bf16_rne(kb * c + ka * s);
+    rope_pair(bf16_to_f32(q[a]), bf16_to_f32(q[b]), c, s, q[a], q[b]);
+    rope_pair(bf16_to_f32(k[a]), bf16_to_f32(k[b]), c, s, kc[a], kc[b]);
   }
   const uint4* vs = reinterpret_cast<const uint4*>(v);
   uint4* vd = reinterpret_cast<uint4*>(vc);
@@ -437,7 +441,7 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(int H, int pos0, co
 }
 
 // Rotary positions, cache append and causal attention of a decode step (T <=
-// kDenseMaxTokens) in one launch, one workgroup of 8 wavefronts per (head,
+// kDenseMaxTokens, up to step_attention_keys) in one launch, one workgroup of 8 wavefronts per (head,
 // token t).  Its query and the keys of tokens 0 .. t are rotated here (angles
 // as in rope_kv_kernel, in fp64), token t's key and value appended to the
 // cache; keys and values of the call's own tokens come from qkv, so no
@@ -447,8 +451,11 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(int H, int pos0, co
 // Bound by latency on H workgroups: the first 512 keys' chunks (a key per
 // thread, spread over the wavefronts) and the first 20 values of every stripe
 // (four dimensions per thread) are on their way before the rotation starts
-// (16 wavefronts had 128 registers each, spilled them and took 22 us).  At 302 keys and 16 heads this and the rotation
-// took 11.4 + 4.2 us as two launches of 4-wavefront workgroups, now 10.3.
+// (16 wavefronts had 128 registers each, spilled them and took 22 us).  At 302
+// keys and 16 heads this and the rotation took 11.4 + 4.2 us as two launches of
+// 4-wavefront workgroups, now 8 to 10.  Values ahead, whole step of four layers
+// against 20: 8 to 28 within 2% at head sizes 64 and 128 from 30 to 900 keys;
+// at 256 8 is 6% and 12 4% slower from 600 keys on, 16 to 28 within 2%.
 constexpr int kAttnThreads = 512;
 template <int kDh>
 __global__ __launch_bounds__(kAttnThreads) void step_attention_kernel(
@@ -501,14 +508,11 @@ __global__ __launch_bounds__(kAttnThreads) void step_attention_kernel(
     rope_cos_sin((double)(pos0 + tt) * rope.inv[i], c, s);
     const uint16_t* row = qkv + (int64_t)tt * 3 * d + h * kDh + i;
     if (tt == t) {
-      const float qa = bf16_to_f32(row[0]), qb = bf16_to_f32(row[half]);
       uint16_t* q16 = reinterpret_cast<uint16_t*>(qs);
-      q16[i] = (uint16_t)f32_to_bf16_rne(qa * c - qb * s);
-      q16[i + half] = (uint16_t)f32_to_bf16_rne(qb * c + qa * s);
+      rope_pair(bf16_to_f32(row[0]), bf16_to_f32(row[half]), c, s, q16[i], q16[i + half]);
     }
-    const float xa = bf16_to_f32(row[d]), xb = bf16_to_f32(row[d + half]);
-    const uint16_t ra = (uint16_t)f32_to_bf16_rne(xa * c - xb * s);
-    const uint16_t rb = (uint16_t)f32_to_bf16_rne(xb * c + xa * s);
+    uint16_t ra, rb;
+    rope_pair(bf16_to_f32(row[d]), bf16_to_f32(row[d + half]), c, s, ra, rb);
     ks[tt][i] = ra;
     ks[tt][i + half] = rb;
     if (tt == t) {
@@ -595,6 +599,16 @@ __global__ __launch_bounds__(kAttnThreads) void step_attention_kernel(
     out[(int64_t)t * d + h * kDh + tid] = (uint16_t)f32_to_bf16_rne(o / sum);
   }
 }
+
+// Positions up to which a decode step takes step_attention_kernel.  Its 512
+// threads read one key row each, so above some rounds their rows no longer
+// share L1 between a row's chunks, and the two launches of 256 threads are
+// faster.  Whole step of four layers against those, d 2048, one token: head
+// size 128 at 500 / 1000 / 1500 / 3000 positions 197 / 234 / 266 / 389 us and
+// 212 / 232 / 254 / 319; 256 at the same 226 / 285 / 343 / 538 and 235 / 283 /
+// 330 / 480; 64 at 1000 / 1500 / 2000 / 3000 205 / 223 / 243 / 295 and 217 /
+// 230 / 243 / 271.
+constexpr int step_attention_keys(int head_dim) { return head_dim == 64 ? 1536 : 1024; }
 
 // Greedy next token: index of the largest logit, ties to the lower index.
 __global__ __launch_bounds__(1024) void argmax_kernel(int V, const float* logits, int32_t* out) {
@@ -702,6 +716,7 @@ struct emoe_decoder {
   std::vector<emoe_cache*> caches;
   uint16_t* kv = nullptr;
   RopeTable rope{};
+  int step_keys = 0;  // steps of more positions take the prompt's attention launches
   rocblas_handle blas = nullptr;
 };
 
@@ -806,6 +821,7 @@ int32_t emoe_decoder_create(const emoe_decoder_dims* dims, const emoe_decoder_we
   dec->w_router.assign(w->w_router, w->w_router + L);
   dec->caches.assign(caches, caches + L);
   dec->kv = static_cast<uint16_t*>(kv_cache);
+  dec->step_keys = step_attention_keys(dims->head_dim);
   for (int i = 0; i < dims->head_dim / 2; ++i)
     dec->rope.inv[i] = std::pow((double)dims->rope_base, -2.0 * (double)i / (double)dims->head_dim);
   const rocblas_status rs = rocblas_create_handle(&dec->blas);
@@ -821,6 +837,14 @@ int32_t emoe_decoder_destroy(emoe_decoder* dec) {
   if (!dec) return EMOE_OK;
   if (dec->blas) (void)rocblas_destroy_handle(dec->blas);
   delete dec;
+  return EMOE_OK;
+}
+
+int32_t emoe_test_set_step_keys(emoe_decoder* dec, int32_t keys) {
+  if (!dec) return report_error(EMOE_EINVAL, "decoder is NULL");
+  if (keys < -1 || keys > EMOE_DECODER_MAX_POSITIONS)
+    return report_error(EMOE_EINVAL, "keys=%d outside [-1, %d]", keys, EMOE_DECODER_MAX_POSITIONS);
+  dec->step_keys = keys < 0 ? step_attention_keys(dec->dims.head_dim) : keys;
   return EMOE_OK;
 }
 
@@ -855,10 +879,11 @@ int32_t emoe_decoder_forward(emoe_decoder* dec, const int32_t* tokens, int32_t T
   const size_t kv_layer = (size_t)2 * D.max_positions * d;
   int32_t st;
   // Decode steps (one to four tokens) take the norm into the QKV projection
-  // and the rotation into the attention; wider rows than one chunk per thread
-  // keep the norm's own launch.
+  // and, up to step_keys positions, the rotation into the attention; wider
+  // rows than one chunk per thread keep the norm's own launch.
   const bool norm_in_gemv = d <= kNormMaxInputs;
   const bool step = T <= kDenseMaxTokens;
+  const bool step_attn = step && pos0 + T <= dec->step_keys;
   for (int l = 0; l < D.n_layers; ++l) {
     uint16_t* kc = dec->kv + (size_t)l * kv_layer;
     uint16_t* vc = kc + (size_t)D.max_positions * d;
@@ -872,7 +897,7 @@ int32_t emoe_decoder_forward(emoe_decoder* dec, const int32_t* tokens, int32_t T
                  dec->attn_norm[l], D.rms_eps, n);
       if ((st = dense(dec, T, 3 * d, d, n, dec->wqkv[l], nullptr, qkv, false, stream))) return st;
     }
-    if (step) {
+    if (step_attn) {
       const dim3 grid(H, T), block(kAttnThreads);
       if (Dh == 64)
         DEC_LAUNCH(step_attention_kernel<64>, grid, block, 0, stream, H, pos0, dec->rope, qkv, kc, vc, attn);

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("heads,head_dim,pos0,tokens", [
     (4, 64, 0, 4), (4, 64, 1025, 1), (4, 64, 127, 2), (2, 128, 0, 1), (2, 128, 1, 3),
     (2, 128, 63, 1), (2, 128, 318, 4), (2, 128, 513, 1), (1, 256, 31, 2), (1, 256, 159, 4),
-    (17, 128, 70, 3)])
+    (17, 128, 70, 3), (1, 256, 513, 1), (1, 256, 510, 4), (2, 128, 1022, 3), (1, 256, 8185, 4)])
 def test_step_over_a_given_cache_matches_the_oracle(heads, head_dim, pos0, tokens):
     """Two layers, so the second layer's norm takes the experts' output."""
     d = heads * head_dim
@@ -51,5 +51,42 @@ def test_step_over_a_given_cache_matches_the_oracle(heads, head_dim, pos0, token
                 w = want[pos0:].reshape(tokens, d)
                 err = np.abs(after[l, which, pos0:pos0 + tokens] - w).max() / np.abs(w).max()
                 assert err <= 2e-2, (l, which, err)
+    finally:
+        gpu.close()
+
+
+# Both sides of the first 512 keys, of 20 values a stripe (640, 320, 160) and of
+# the last position of the default rule (1536; 1024 above head size 64), head
+# size 256 with its key row in several parts and more than one round, and the
+# longest cache.
+@pytest.mark.parametrize("heads,head_dim,pos0,tokens", [
+    (2, 64, 0, 4), (2, 64, 637, 4), (2, 64, 1535, 1), (2, 64, 4001, 3), (1, 128, 0, 1),
+    (1, 128, 509, 4), (2, 128, 1023, 1), (1, 128, 2099, 2), (1, 256, 158, 4), (1, 256, 510, 4),
+    (1, 256, 513, 1), (1, 256, 1025, 2), (1, 256, 8188, 4)])
+def test_step_attention_gives_the_bits_of_the_prompt_launches(heads, head_dim, pos0, tokens):
+    """The one-launch rotation and attention of a step against the rotation
+    and attention launches of prompts: logits, token and cache bit for bit."""
+    d = heads * head_dim
+    shape = D.DecoderShape(n_layers=2, d_model=d, n_heads=heads, head_dim=head_dim, vocab=300,
+                           d_ff=128, n_experts=4, top_k=2)
+    m = _model(shape, seed=43)
+    max_pos = pos0 + tokens
+    gpu = GpuDecoder(shape, m, 4, max_positions=max_pos, max_tokens=4)
+    try:
+        rng = np.random.default_rng(pos0 + tokens)
+        past = np.zeros((2, 2, max_pos, d), np.uint16)
+        past[:, :, :pos0] = f32_to_bf16_bits(rng.standard_normal((2, 2, pos0, d)).astype(np.float32))
+        seq = list(rng.integers(0, 300, tokens))
+        out = []
+        for keys in (max_pos, max_pos - 1, -1):   # one launch, two, the rule's choice
+            gpu.dec.set_step_keys(keys)
+            gpu.kv.copy_(dev(past).view(torch.uint8).reshape(-1))
+            gpu.logits.fill_(float("nan"))
+            logits, tok = gpu.run(seq, pos0)
+            out.append((logits.view(np.uint32), tok, gpu.kv.cpu().numpy().copy()))
+        assert np.isfinite(out[0][0].view(np.float32)).all()
+        for got in out[1:]:
+            assert np.array_equal(got[0], out[0][0]) and got[1] == out[0][1]
+            assert np.array_equal(got[2], out[0][2])
     finally:
         gpu.close()
