@@ -367,25 +367,31 @@ __device__ __forceinline__ void wave_topk(const float* __restrict__ z, int n_exp
   wave_topk_weights<kCoStore>(st, n_experts, top_k, renormalize, w_out);
 }
 
+// Exclusive sum over the wavefront's lanes with DPP lane moves (row shifts by
+// 1, 2, 4 and 8, then the two row broadcasts); lanes that a move does not
+// reach add 0.  Every lane must be active.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ int dpp_add_i32(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, kCtrl, kRowMask, 0xF, false);
+}
+
 __device__ __forceinline__ int wave_exclusive_scan(int v, int& total) {
-  const int lane = lane_id();
   int x = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(x, off);
-    if (lane >= off) x += y;
-  }
-  total = __shfl(x, 63);
+  x = dpp_add_i32<0x111, 0xF>(x);  // row_shr:1
+  x = dpp_add_i32<0x112, 0xF>(x);  // row_shr:2
+  x = dpp_add_i32<0x114, 0xF>(x);  // row_shr:4
+  x = dpp_add_i32<0x118, 0xF>(x);  // row_shr:8
+  x = dpp_add_i32<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
+  x = dpp_add_i32<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
+  total = __builtin_amdgcn_readlane(x, 63);
   return x - v;
 }
 
 // LDS of the block-wide grouping: per wavefront and expert, first the
-// wavefront's count, then its first grouped position; and the sums (pairs,
-// active experts, row tiles) of each block of 64 experts.
+// wavefront's count, then its first grouped position.
 template <int kThreads>
 struct GroupShared {
   int wbase[kThreads / 64][EMOE_MAX_EXPERTS];
-  int block_sum[kPerLane][3];
 };
 
 // Lanes of the wavefront whose expert equals this lane's (valid lanes only),
@@ -456,56 +462,99 @@ __device__ __forceinline__ void block_group(
   }
   __syncthreads();
 
-  // Totals, offsets, active list, row tiles; then each wavefront's base.
-  // Wavefront b scans experts 64b + lane, one round of LDS reads; above 64
-  // experts the blocks' sums meet through LDS.  The chain of a block is the
-  // whole cost: four neighbouring experts a lane on one wavefront took 1.1 us
-  // more at 64 experts, the blocks one after the other on one wavefront 1.6 us
-  // more at 256.
-  static_assert(kWaves >= kPerLane, "a wavefront per block of 64 experts");
-  const int blocks = (n_experts + 63) / 64;
-  const int e = 64 * wave + lane;
-  const bool ok = e < n_experts;
-  int own[kWaves], c = 0, at = 0, nz_at = 0, tl_at = 0;
-  int total = 0, nz_total = 0, tl_total = 0;
-  if (wave < blocks) {
+  // Totals, offsets, active list, row tiles; then each wavefront's base, one
+  // block of 64 experts at a time, one per lane: the chain of a block (a round
+  // of LDS reads, the scans) is the cost.  With 16 wavefronts every block has
+  // one of its own and the blocks' sums meet in LDS (256 experts, one after
+  // the other: 0.45 us more; with lane exchanges through LDS in the scans 1.6).
+  // The four of the fused decode launch leave the blocks to the first one: its
+  // code is cold, and the code for several wavefronts cost it 0.15 us at 64
+  // experts, four neighbouring experts a lane 1.1 us.
+  constexpr bool kWavePerBlock = kWaves >= 16;
+  if constexpr (kWavePerBlock) {
+    __shared__ int block_sum[kPerLane][3];  // pairs, active experts, row tiles
+    const int blocks = (n_experts + 63) / 64;
+    const bool ok = tid < n_experts;
+    int own[kWaves], c = 0, at = 0, nz_at = 0, tl_at = 0;
+    int total = 0, nz_total = 0, tl_total = 0;
+    if (wave < blocks) {
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) own[w] = ok ? sh.wbase[w][e] : 0;
+      for (int w = 0; w < kWaves; ++w) own[w] = ok ? sh.wbase[w][tid] : 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) c += own[w];
-    at = wave_exclusive_scan(c, total);
-    nz_at = wave_exclusive_scan(c > 0, nz_total);
-    tl_at = wave_exclusive_scan(mfma_row_tiles(c, mfma_rows), tl_total);
-    if (blocks > 1 && lane == 0) {
-      sh.block_sum[wave][0] = total;
-      sh.block_sum[wave][1] = nz_total;
-      sh.block_sum[wave][2] = tl_total;
+      for (int w = 0; w < kWaves; ++w) c += own[w];
+      at = wave_exclusive_scan(c, total);
+      nz_at = wave_exclusive_scan(c > 0, nz_total);
+      tl_at = wave_exclusive_scan(mfma_row_tiles(c, mfma_rows), tl_total);
     }
-  }
-  if (blocks > 1) __syncthreads();
-  if (wave < blocks) {
-    int base = 0, nz_base = 0, tl_base = 0;
-    for (int b = 0; b < wave; ++b) {
-      base += sh.block_sum[b][0];
-      nz_base += sh.block_sum[b][1];
-      tl_base += sh.block_sum[b][2];
+    if (blocks > 1) {
+      if (wave < blocks && lane == 0) {
+        block_sum[wave][0] = total;
+        block_sum[wave][1] = nz_total;
+        block_sum[wave][2] = tl_total;
+      }
+      __syncthreads();
+      int base = 0, nz_base = 0, tl_base = 0;
+      for (int b = 0; b < wave && b < blocks; ++b) {
+        base += block_sum[b][0];
+        nz_base += block_sum[b][1];
+        tl_base += block_sum[b][2];
+      }
+      at += base;
+      nz_at += nz_base;
+      tl_at += tl_base;
     }
     if (ok) {
-      st_u32<kCo>(counts + e, (uint32_t)c);
-      st_u32<kCo>(offsets + e, (uint32_t)(base + at));
-      if (tile_offsets) st_u32<kCo>(tile_offsets + e, (uint32_t)(tl_base + tl_at));
-      if (c > 0) st_u32<kCo>(active + nz_base + nz_at, (uint32_t)e);
-      int run = base + at;
+      st_u32<kCo>(counts + tid, (uint32_t)c);
+      st_u32<kCo>(offsets + tid, (uint32_t)at);
+      if (tile_offsets) st_u32<kCo>(tile_offsets + tid, (uint32_t)tl_at);
+      if (c > 0) st_u32<kCo>(active + nz_at, (uint32_t)tid);
+      int run = at;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) {
-        sh.wbase[w][e] = run;
+        sh.wbase[w][tid] = run;
         run += own[w];
       }
     }
+    // Lane 0's exclusive sums are those of the blocks before its own.
     if (wave == blocks - 1 && lane == 0) {
-      st_u32<kCo>(offsets + n_experts, (uint32_t)(base + total));
-      if (tile_offsets) st_u32<kCo>(tile_offsets + n_experts, (uint32_t)(tl_base + tl_total));
-      st_u32<kCo>(n_active, (uint32_t)(nz_base + nz_total));
+      st_u32<kCo>(offsets + n_experts, (uint32_t)(at + total));
+      if (tile_offsets) st_u32<kCo>(tile_offsets + n_experts, (uint32_t)(tl_at + tl_total));
+      st_u32<kCo>(n_active, (uint32_t)(nz_at + nz_total));
+    }
+  } else if (wave == 0) {
+    int base = 0, nz_base = 0, tl_base = 0;
+    for (int e0 = 0; e0 < n_experts; e0 += 64) {
+      const int e = e0 + lane;
+      const bool ok = e < n_experts;
+      int own[kWaves], c = 0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) own[w] = ok ? sh.wbase[w][e] : 0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) c += own[w];
+      int total, nz_total, tl_total;
+      const int at = base + wave_exclusive_scan(c, total);
+      const int nz_at = nz_base + wave_exclusive_scan(c > 0, nz_total);
+      const int tl_at = tl_base + wave_exclusive_scan(mfma_row_tiles(c, mfma_rows), tl_total);
+      if (ok) {
+        st_u32<kCo>(counts + e, (uint32_t)c);
+        st_u32<kCo>(offsets + e, (uint32_t)at);
+        if (tile_offsets) st_u32<kCo>(tile_offsets + e, (uint32_t)tl_at);
+        if (c > 0) st_u32<kCo>(active + nz_at, (uint32_t)e);
+        int run = at;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+          sh.wbase[w][e] = run;
+          run += own[w];
+        }
+      }
+      base += total;
+      nz_base += nz_total;
+      tl_base += tl_total;
+    }
+    if (lane == 0) {
+      st_u32<kCo>(offsets + n_experts, (uint32_t)base);
+      if (tile_offsets) st_u32<kCo>(tile_offsets + n_experts, (uint32_t)tl_base);
+      st_u32<kCo>(n_active, (uint32_t)nz_base);
     }
   }
   __syncthreads();

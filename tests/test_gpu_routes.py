@@ -98,19 +98,18 @@ def test_many_row_tiles_match_the_gemv_path(shape, tokens, skew):
 # one-workgroup grouping (1024) and of a pass over the chunk counts (64 chunks
 # above 64 experts, 256 below); k = 5 takes the counts' own launch.
 @pytest.mark.parametrize("experts", [64, 65, 128, 129, 192, 193, 256])
-@pytest.mark.parametrize("tokens,k", [(1, 8), (128, 8), (129, 8), (207, 5), (512, 8), (513, 8),
-                                      (2100, 8), (64, 17)])
+@pytest.mark.parametrize("tokens,k", [(1, 8), (4, 8), (128, 8), (129, 8), (207, 5), (512, 8),
+                                      (513, 8), (2100, 8), (64, 17)])
 def test_grouping_over_blocks_of_experts_equals_the_oracle(experts, tokens, k):
-    """Every array of the grouping, in a layer call and in emoe_route; a third
-    of the experts never chosen, so the active list has gaps in every block."""
+    """Every array of the grouping, in a layer call (up to 4 tokens also the
+    fused launch) and in emoe_route; a third of the experts never chosen, so
+    the active list has gaps in every block."""
     shape = LayerShape(128, 128, experts, k)
     lay = make_layer(shape, tokens, seed=17)
     layer = Layer(dims_of(shape), lay, tokens)
     rng = np.random.default_rng([experts, tokens])
     z = rng.standard_normal((tokens, experts)).astype(np.float32)
     z[:, ::3] -= 50
-    layer.ws.fill_(0xA5)
-    layer.forward(lay.h, logits=z, path=api.EMOE_PATH_MFMA)
     pairs = tokens * k
     ids = O.topk_experts(z, k)
     gr = O.group_by_expert(ids, experts)
@@ -120,9 +119,15 @@ def test_grouping_over_blocks_of_experts_equals_the_oracle(experts, tokens, k):
     want = dict(topk_ids=ids.reshape(-1), counts=gr.counts, offsets=gr.offsets,
                 sorted_pairs=gr.sorted_pairs, active=gr.active, n_active=[len(gr.active)],
                 tile_offsets=tiles, pair_pos=pos)
-    for name, w in want.items():
-        got = layer.ws_array(name, len(w), np.int32)
-        assert np.array_equal(got, np.asarray(w, np.int32)), name
+    for path in (api.EMOE_PATH_MFMA, api.EMOE_PATH_AUTO):
+        layer.ws.fill_(0xA5)
+        st = api.Stats()
+        layer.forward(lay.h, logits=z, path=path, stats=st)
+        fused = st.kernel_launches == 1   # writes no row tiles
+        assert fused == (tokens <= 4 and path == api.EMOE_PATH_AUTO)
+        for name, w in want.items():
+            got = layer.ws_array(name, len(w), np.int32)
+            assert (fused and name == "tile_offsets") or np.array_equal(got, np.asarray(w, np.int32)), name
     i32 = lambda n: torch.full((n,), -1, dtype=torch.int32, device="cuda:0")
     out = dict(topk_ids=i32(pairs), counts=i32(experts), offsets=i32(experts + 1),
                sorted_pairs=i32(pairs), active=i32(experts), n_active=i32(1))
