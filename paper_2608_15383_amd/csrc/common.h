@@ -305,12 +305,16 @@ hipError_t launch_topk(int tokens, int n_experts, int top_k, int renormalize,
 // The row sums as a launch of their own.
 hipError_t launch_row_bias(int tokens, RowBias rb, hipStream_t stream);
 
-// launch_topk and launch_group in one launch.  Against the separate launches a
-// layer call gains 0.3 to 1.0 us at 5 to 8 tokens and 0.1 to 0.8 at 12 with 8 to
-// 64 experts; it loses 0.1 to 0.8 us at 16 tokens, 2.5 to 3 at 32 and 7 to 8 at
-// 64 there, and above 64 experts (top_k rounds of wavefront maxima per token)
-// up to 1 us at 5 to 8 tokens, 4 at 16 and 32 at 64 (256 experts, top-16).
-constexpr bool topk_group_fits(int tokens, int n_experts) { return tokens <= 12 && n_experts <= 64; }
+// launch_topk and launch_group in one launch, while each of its 16 wavefronts
+// has at most one token.  Against the two launches, up to 64 experts: a layer
+// call's kernels take 0.3 to 1.0 us less at 5 to 8 tokens and from 0.1 less to
+// 0.8 more at 16, and a call has one launch less to enqueue, which sets the pace
+// of small layers (16 tokens, d 256, 8 experts: 22.5 against 25.0 us).  From two
+// tokens a wavefront on it loses: 0.3 to 1.2 us at 17 tokens, 2.5 to 3 at 32, 7
+// to 8 at 64; above 64 experts, where a token's top-k is top_k rounds of
+// wavefront maxima, up to 1 us at 5 to 8 tokens, 4 at 16 and 32 at 64 (256
+// experts, top-16).
+constexpr bool topk_group_fits(int tokens, int n_experts) { return tokens <= 16 && n_experts <= 64; }
 hipError_t launch_topk_group(int tokens, int n_experts, int top_k, int renormalize,
                              const LogitSource& src, int32_t* topk_ids, float* topk_w,
                              int32_t* counts, int32_t* offsets, int32_t* sorted_pairs,

@@ -414,7 +414,7 @@ __device__ __forceinline__ uint64_t match_expert(bool valid, int e, int bits) {
 // Each wavefront owns a contiguous range of 64-pair chunks: pass 1 counts its
 // pairs per expert, a scan turns the counts into each wavefront's first
 // position per expert, and pass 2 places its pairs in order.
-template <int kThreads, bool kCo>
+template <int kThreads, bool kCo, bool kWavePerBlock>
 __device__ __forceinline__ void block_group(
     GroupShared<kThreads>& sh, int pairs, int n_experts, const int32_t* __restrict__ ids,
     int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
@@ -425,6 +425,7 @@ __device__ __forceinline__ void block_group(
   const int tid = threadIdx.x;
   const int lane = lane_id();
   const int wave = tid >> 6;
+  static_assert(!kWavePerBlock || kWaves >= kPerLane, "a wavefront per block of 64 experts");
   int bits = 0;
   while ((1 << bits) < n_experts) ++bits;
   const int n_chunks = (pairs + 63) / 64;
@@ -464,13 +465,13 @@ __device__ __forceinline__ void block_group(
 
   // Totals, offsets, active list, row tiles; then each wavefront's base, one
   // block of 64 experts at a time, one per lane: the chain of a block (a round
-  // of LDS reads, the scans) is the cost.  With 16 wavefronts every block has
-  // one of its own and the blocks' sums meet in LDS (256 experts, one after
-  // the other: 0.45 us more; with lane exchanges through LDS in the scans 1.6).
-  // The four of the fused decode launch leave the blocks to the first one: its
-  // code is cold, and the code for several wavefronts cost it 0.15 us at 64
-  // experts, four neighbouring experts a lane 1.1 us.
-  constexpr bool kWavePerBlock = kWaves >= 16;
+  // of LDS reads, the scans) is the cost.  With kWavePerBlock every block has
+  // a wavefront of its own and the blocks' sums meet in LDS (256 experts, one
+  // after the other: 0.45 us more; with lane exchanges through LDS in the
+  // scans 1.6).  Without it the first wavefront takes them in turn: the fused
+  // decode launch, where the code for several wavefronts, which runs cold,
+  // cost 0.15 us at 64 experts and four neighbouring experts a lane 1.1 us, and
+  // the top-k with grouping, which has one block (0.2 us).
   if constexpr (kWavePerBlock) {
     __shared__ int block_sum[kPerLane][3];  // pairs, active experts, row tiles
     const int blocks = (n_experts + 63) / 64;

@@ -253,14 +253,14 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(
     int32_t* __restrict__ n_active, int32_t* __restrict__ tile_offsets,
     int32_t* __restrict__ pair_pos, int mfma_rows) {
   __shared__ GroupShared<kGroupThreads> sh;
-  block_group<kGroupThreads, false>(sh, pairs, n_experts, ids, counts, offsets, sorted_pairs,
-                                    active, n_active, tile_offsets, pair_pos, mfma_rows);
+  block_group<kGroupThreads, false, true>(sh, pairs, n_experts, ids, counts, offsets, sorted_pairs,
+                                          active, n_active, tile_offsets, pair_pos, mfma_rows);
 }
 
 // Top-k and grouping of a small call in one launch: workgroup 0's 16
-// wavefronts take the tokens in turn, then group all pairs.  It saves a
-// launch's start, its gap and a round trip of the ids, and pays for a top-k
-// of all tokens on one CU, so only calls that topk_group_fits admits take it.
+// wavefronts take the tokens, then group all pairs.  It saves a launch's
+// start, its gap and a round trip of the ids, and pays for a top-k of all
+// tokens on one CU, so only calls that topk_group_fits admits take it.
 __global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(
     int tokens, int n_experts, int top_k, int renormalize, LogitSource src,
     int32_t* __restrict__ topk_ids, float* __restrict__ topk_w, int32_t* __restrict__ counts,
@@ -279,8 +279,9 @@ __global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(
   }
   __threadfence_block();
   __syncthreads();
-  block_group<kGroupThreads, false>(sh, tokens * top_k, n_experts, topk_ids, counts, offsets,
-                                    sorted_pairs, active, n_active, tile_offsets, pair_pos, mfma_rows);
+  block_group<kGroupThreads, false, false>(sh, tokens * top_k, n_experts, topk_ids, counts, offsets,
+                                           sorted_pairs, active, n_active, tile_offsets, pair_pos,
+                                           mfma_rows);
 }
 
 // Grouping spread over many workgroups (large calls): 64-pair chunks, one per

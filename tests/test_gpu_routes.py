@@ -23,7 +23,7 @@ def _y_ref(lay, r, k):
 
 
 # One, two and four slices of d and none (d not a multiple of 512); tokens on
-# both sides of the fused top-k and grouping (12, and 64 experts) and of the
+# both sides of the fused top-k and grouping (16, and 64 experts) and of the
 # wide grouping (1024 pairs), with k dividing 64 or not; a partial token and
 # expert tile.
 @pytest.mark.parametrize("shape,tokens", [
@@ -31,9 +31,9 @@ def _y_ref(lay, r, k):
     (LayerShape(2048, 128, 64, 8), 17), (LayerShape(2048, 128, 200, 8), 64),
     (LayerShape(1024, 128, 64, 8), 65), (LayerShape(640, 128, 12, 3), 64),
     (LayerShape(640, 128, 12, 3), 343), (LayerShape(384, 128, 16, 8), 130),
-    (LayerShape(2048, 128, 16, 8), 129), (LayerShape(1024, 128, 64, 8), 12),
-    (LayerShape(1024, 128, 64, 64), 12), (LayerShape(640, 128, 64, 8), 13),
-    (LayerShape(1024, 128, 65, 8), 12)])
+    (LayerShape(2048, 128, 16, 8), 129), (LayerShape(1024, 128, 64, 8), 16),
+    (LayerShape(1024, 128, 64, 64), 16), (LayerShape(640, 128, 64, 8), 17),
+    (LayerShape(1024, 128, 65, 8), 16)])
 @pytest.mark.parametrize("given", [False, True])
 def test_layer_routing_equals_the_oracle(shape, tokens, given):
     """Logits, ids, weights and grouping of a layer call on the MFMA path, and
@@ -60,9 +60,9 @@ def test_layer_routing_equals_the_oracle(shape, tokens, given):
 
 
 @pytest.mark.parametrize("experts,tokens,launches", [
-    (64, 5, 5), (64, 12, 5), (64, 13, 6), (64, 64, 6), (65, 12, 6), (200, 5, 6), (8, 12, 5), (8, 16, 6)])
+    (64, 5, 5), (64, 16, 5), (64, 17, 6), (64, 64, 6), (65, 16, 6), (200, 5, 6), (8, 16, 5), (8, 17, 6)])
 def test_one_routing_launch_only_for_the_smallest_calls(experts, tokens, launches):
-    """Above 12 tokens or 64 experts the top-k keeps its own launch: all tokens
+    """Above 16 tokens or 64 experts the top-k keeps its own launch: all tokens
     on one compute unit cost more there than the launch saved."""
     shape = LayerShape(512, 128, experts, 4)
     lay = make_layer(shape, tokens, seed=5)
