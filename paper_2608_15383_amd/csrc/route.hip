@@ -116,10 +116,11 @@ __global__ __launch_bounds__(256) void router_logits_kernel(int tokens, int n_ex
   }
 }
 
-// Selection from token t's logits: as given, or (src.slices > 0) the router's
-// slice sums added in order and rounded to fp32, which are then also stored
-// as the call's logits.  One selection after either source: a copy of it per
-// source made the top-k launches 0.2 to 0.6 us longer.
+// Selection from token t's logits: as given, or (kParts) the router's slice
+// sums added in order and rounded to fp32, which are then also stored as the
+// call's logits.  A kernel per source: with both in one, either as two
+// selections or behind one branch, the top-k launches took 0.2 to 0.6 us more.
+template <bool kParts>
 __device__ __forceinline__ void topk_select_from(const LogitSource& src, int t, int tokens,
                                                  int n_experts, int top_k, TopkState& st,
                                                  uint64_t* scratch) {
@@ -129,7 +130,7 @@ __device__ __forceinline__ void topk_select_from(const LogitSource& src, int t, 
     const int e = lane + 64 * c;
     st.v[c] = 0.f;
     if (e >= n_experts) continue;
-    if (src.slices == 0) {
+    if constexpr (!kParts) {
       st.v[c] = src.logits[(int64_t)t * n_experts + e];
       continue;
     }
@@ -188,6 +189,7 @@ __global__ __launch_bounds__(256) void row_bias_kernel(int tokens, RowBias rb) {
   row_bias_block(rb, tokens);
 }
 
+template <bool kParts>
 __global__ __launch_bounds__(256) void topk_kernel(int tokens, int n_experts, int top_k,
                                                    int renormalize, LogitSource src,
                                                    int32_t* __restrict__ topk_ids,
@@ -197,7 +199,7 @@ __global__ __launch_bounds__(256) void topk_kernel(int tokens, int n_experts, in
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= tokens) return;
   TopkState st;
-  topk_select_from(src, t, tokens, n_experts, top_k, st, s_rank[threadIdx.x >> 6]);
+  topk_select_from<kParts>(src, t, tokens, n_experts, top_k, st, s_rank[threadIdx.x >> 6]);
   wave_topk_store_ids<false>(st, top_k, topk_ids + (int64_t)t * top_k);
   wave_topk_weights<false>(st, n_experts, top_k, renormalize, topk_w + (int64_t)t * top_k);
 }
@@ -207,6 +209,7 @@ __global__ __launch_bounds__(256) void topk_kernel(int tokens, int n_experts, in
 // wide grouping (chunk c = blockIdx.x), and after its selections it also
 // writes that chunk's per-expert counts (chunk_count_kernel's row), which
 // saves that launch.  Ids and weights as topk_kernel writes them.
+template <bool kParts>
 __global__ __launch_bounds__(1024) void topk_count_kernel(int tokens, int n_experts, int top_k,
                                                           int renormalize, LogitSource src,
                                                           int32_t* __restrict__ topk_ids,
@@ -225,7 +228,7 @@ __global__ __launch_bounds__(1024) void topk_count_kernel(int tokens, int n_expe
   for (int e = threadIdx.x; e < n_experts; e += blockDim.x) row[e] = 0;
   if (t < tokens) {
     TopkState st;
-    topk_select_from(src, t, tokens, n_experts, top_k, st, s_rank[wave]);
+    topk_select_from<kParts>(src, t, tokens, n_experts, top_k, st, s_rank[wave]);
     wave_topk_store_ids<false>(st, top_k, topk_ids + (int64_t)t * top_k);
 #pragma unroll
     for (int r = 0; r < kPerLane; ++r)
@@ -261,6 +264,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(
 // wavefronts take the tokens, then group all pairs.  It saves a launch's
 // start, its gap and a round trip of the ids, and pays for a top-k of all
 // tokens on one CU, so only calls that topk_group_fits admits take it.
+template <bool kParts>
 __global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(
     int tokens, int n_experts, int top_k, int renormalize, LogitSource src,
     int32_t* __restrict__ topk_ids, float* __restrict__ topk_w, int32_t* __restrict__ counts,
@@ -273,7 +277,7 @@ __global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(
   const int wave = threadIdx.x >> 6;
   for (int t = wave; t < tokens; t += kGroupThreads / 64) {
     TopkState st;
-    topk_select_from(src, t, tokens, n_experts, top_k, st, s_rank[wave]);
+    topk_select_from<kParts>(src, t, tokens, n_experts, top_k, st, s_rank[wave]);
     wave_topk_store_ids<false>(st, top_k, topk_ids + (int64_t)t * top_k);
     wave_topk_weights<false>(st, n_experts, top_k, renormalize, topk_w + (int64_t)t * top_k);
   }
@@ -338,25 +342,28 @@ __global__ __launch_bounds__(64 * kChunkWaves) void chunk_place_kernel(
   auto sum_chunks = [&](auto blocks_c) __attribute__((always_inline)) {
     constexpr int kQ = decltype(blocks_c)::value;
     constexpr int kBatch = 16 / kQ;
-    int all[kQ], pre[kQ], mine[kQ];  // mine: chunk c0 + wave, one of the wavefront's own
+    int at[kQ], all[kQ], pre[kQ], mine[kQ];
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) all[q] = pre[q] = mine[q] = 0;
+    for (int q = 0; q < kQ; ++q) {
+      at[q] = min(64 * q + lane, n_experts - 1);  // lanes past the end repeat it, unused
+      all[q] = pre[q] = 0;
+      mine[q] = c0 + wave < n_chunks ? chunk_counts[(int64_t)(c0 + wave) * n_experts + at[q]] : 0;
+    }
     for (int cb = wave; cb < n_chunks; cb += kBatch * kChunkWaves) {
       int v[kBatch][kQ];
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j)
+      for (int j = 0; j < kBatch; ++j) {
+        const int c = cb + j * kChunkWaves;
 #pragma unroll
-        for (int q = 0; q < kQ; ++q) {
-          const int c = cb + j * kChunkWaves, e = 64 * q + lane;
-          v[j][q] = c < n_chunks && e < n_experts ? chunk_counts[(int64_t)c * n_experts + e] : 0;
-        }
+        for (int q = 0; q < kQ; ++q)
+          v[j][q] = c < n_chunks ? chunk_counts[(int64_t)c * n_experts + at[q]] : 0;
+      }
 #pragma unroll
       for (int j = 0; j < kBatch; ++j)
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
           all[q] += v[j][q];
           if (cb + j * kChunkWaves < c0) pre[q] += v[j][q];
-          if (cb + j * kChunkWaves == c0 + wave) mine[q] = v[j][q];
         }
     }
 #pragma unroll
@@ -506,8 +513,8 @@ hipError_t launch_topk(int tokens, int n_experts, int top_k, int renormalize,
                        RowBias rb) {
   if (tokens == 0) return hipSuccess;
   const dim3 grid = bias_grid(rb, (tokens + 3) / 4, tokens, 4);
-  launch(topk_kernel, grid, dim3(256), stream, tokens, n_experts, top_k, renormalize, src, topk_ids,
-         topk_w, rb);
+  launch(src.slices ? topk_kernel<true> : topk_kernel<false>, grid, dim3(256), stream, tokens,
+         n_experts, top_k, renormalize, src, topk_ids, topk_w, rb);
   return hipGetLastError();
 }
 
@@ -518,8 +525,8 @@ hipError_t launch_topk_count(int tokens, int n_experts, int top_k, int renormali
   if (top_k < 1 || 64 % top_k != 0 || 64 / top_k > 16) return hipErrorInvalidValue;
   const int per = 64 / top_k;  // tokens (wavefronts) per chunk
   const dim3 grid = bias_grid(rb, (tokens + per - 1) / per, tokens, per);
-  launch(topk_count_kernel, grid, dim3(64 * per), stream, tokens, n_experts, top_k, renormalize, src,
-         topk_ids, topk_w, chunk_counts, rb);
+  launch(src.slices ? topk_count_kernel<true> : topk_count_kernel<false>, grid, dim3(64 * per),
+         stream, tokens, n_experts, top_k, renormalize, src, topk_ids, topk_w, chunk_counts, rb);
   return hipGetLastError();
 }
 
@@ -531,9 +538,9 @@ hipError_t launch_topk_group(int tokens, int n_experts, int top_k, int renormali
                              RowBias rb) {
   if (tokens == 0) return hipSuccess;
   const dim3 grid = bias_grid(rb, 1, tokens, kGroupThreads / 64);
-  launch(topk_group_kernel, grid, dim3(kGroupThreads), stream, tokens, n_experts, top_k, renormalize,
-         src, topk_ids, topk_w, counts, offsets, sorted_pairs, active, n_active, tile_offsets, pair_pos,
-         mfma_rows, rb);
+  launch(src.slices ? topk_group_kernel<true> : topk_group_kernel<false>, grid,
+         dim3(kGroupThreads), stream, tokens, n_experts, top_k, renormalize, src, topk_ids, topk_w,
+         counts, offsets, sorted_pairs, active, n_active, tile_offsets, pair_pos, mfma_rows, rb);
   return hipGetLastError();
 }
 
