@@ -141,9 +141,6 @@ __device__ __forceinline__ uint32_t ld_u32(const void* p) {
 template <bool kCo>
 __device__ __forceinline__ int32_t ld_i32(const int32_t* p) { return (int32_t)ld_u32<kCo>(p); }
 
-template <bool kCo>
-__device__ __forceinline__ float ld_f32(const float* p) { return __uint_as_float(ld_u32<kCo>(p)); }
-
 // 16-byte loads from one buffer (base pointer uniform across the wavefront).
 // The coherent form is a raw buffer load with the sc1 cache policy.
 template <bool kCo>
