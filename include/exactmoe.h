@@ -105,7 +105,9 @@ typedef struct emoe_ws_layout {
   size_t pair_pos;      /* i32   [T*k]    grouped position of each pair id */
   size_t act;           /* bf16  [T*k][d_ff]    phi(g)*u per pair, grouped order */
   size_t pair_out;      /* expert output per pair id, [T*k][d_model]: f32 on the GEMV and
-                           mixed paths, bf16 (in the first half of the field) on the MFMA path */
+                           mixed paths, bf16 (in the first half of the field) on the MFMA path;
+                           until the down projection writes it, the router's f64 sums over
+                           slices of d, [slice][T][E], in calls that split the router */
   size_t act_bias;      /* f32   [d_ff/128][T*k]    -136 * group sums of act, by grouped
                                                       position (MFMA kernels) */
   size_t chunk_counts;  /* i32   [ceil(T*k/64)][E]  pairs per expert in each 64-pair chunk
@@ -356,7 +358,11 @@ int32_t emoe_debug_fused_plan(const emoe_dims* dims, int32_t tokens, int32_t cap
                               int32_t* plan, int32_t* work, int32_t max_workers);
 
 /* ---------------------------------------------------------------- kernel timing */
-/* Kernels launched by the layer calls, as reported by emoe_profile_end. */
+/* Kernels launched by the layer calls, as reported by emoe_profile_end.  A
+ * layer call of at most 16 tokens and 64 experts groups inside EMOE_K_TOPK
+ * and reports no EMOE_K_GROUP (the mixed path and emoe_route always do);
+ * EMOE_K_ROW_BIAS appears on the mixed path only, elsewhere the row sums are
+ * part of EMOE_K_ROUTER or EMOE_K_TOPK. */
 enum emoe_kernel {
   EMOE_K_ROUTER = 0, EMOE_K_TOPK = 1, EMOE_K_GROUP = 2, EMOE_K_GATEUP_GEMV = 3,
   EMOE_K_DOWN_GEMV = 4, EMOE_K_GATEUP_MFMA = 5, EMOE_K_DOWN_MFMA = 6, EMOE_K_COMBINE = 7,

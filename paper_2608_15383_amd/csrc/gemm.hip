@@ -16,15 +16,16 @@
 //    XOR-swizzled by the row index, which makes the MFMA A-fragment reads free
 //    of bank conflicts.  The wavefront's 64 scales are one 8-byte load per
 //    lane, so a group costs each wavefront 9 vector memory instructions,
-//    issued in four parts spread over the previous group's k-steps; a tile of
-//    at most 32 rows leaves out the copies of the others.
+//    issued in four parts spread over the previous group's k-steps; after the
+//    first group, a tile of at most 32 rows leaves out the copies of the
+//    others.
 //  - A tile's start is a chain of latencies (its expert and rows, its token
 //    ids, its first group): one round for the first, one id per lane passed
 //    on by lane moves, and the bias table copied straight into LDS beside the
-//    first group.  At 16 and 113 tokens, where each workgroup has one tile,
-//    gate/up took 29.2 and 32.7 us and down 16.8 and 19.1 before these and the
-//    shorter copies, 27.6 and 31.0, 15.5 and 17.9 now; 777 tokens 73.5 and
-//    42.4 against 71.5 and 41.3.
+//    first group.  Before these and the shorter copies, gate/up took 29.2 us
+//    and down 16.8 at 16 tokens, where each workgroup has one tile, now 27.6
+//    and 15.5; at 113 tokens 32.7 and 19.1, now 31.0 and 17.9; at 777 tokens
+//    73.5 and 42.4, now 71.5 and 41.3.
 //  - Each dword of codes expands in registers to one B operand of
 //    v_mfma_f32_16x16x32_bf16 (record layout in common.h): the codes enter as
 //    bf16 (128 + u), and the chain of four MFMAs of a group starts from the

@@ -30,10 +30,12 @@ typedef double f64x4_t __attribute__((ext_vector_type(4)));
 // added in wavefront order and rounded once to fp32.
 // With parts (gridDim.z = S slices of d) the workgroup covers slice
 // blockIdx.z only and stores its fp64 sum to parts[slice][t][e] instead; the
-// top-k adds the slices in order and rounds.  A tile is 512 MFMAs of 64
-// cycles in a dependent chain per SIMD at d = 2048, so the few tiles of a
-// small call are bound by that chain and by the load rounds between, on as
-// few CUs: 16 tokens took 10.6 us on 4 workgroups.
+// top-k adds the slices in order and rounds (another order of fp64 sums than
+// one workgroup's, so a logit could differ in its last fp32 bit; none has).
+// Each of a tile's wavefronts is a dependent chain of 128 MFMAs of 64 cycles
+// at d = 2048, so the few tiles of a small call are bound by that chain and by
+// the load rounds between, on as few CUs: 16 tokens took 9.3 us on 4
+// workgroups, 4.3 with four slices.
 __global__ __launch_bounds__(256) void router_logits_kernel(int tokens, int n_experts, int d,
                                                             const uint16_t* __restrict__ h,
                                                             const uint16_t* __restrict__ wr,
@@ -58,8 +60,8 @@ __global__ __launch_bounds__(256) void router_logits_kernel(int tokens, int n_ex
   constexpr int kAhead = 4;
   const int n = kq / 32;
   // With tok_bias (d a multiple of 512 per slice, so every iteration of the
-  // loop below is one 128-input group), the first expert tile's workgroups also sum each
-  // group of their token rows.
+  // loop below is one 128-input group), the first expert tile's workgroups
+  // also sum each group of their token rows.
   const bool sums = tok_bias != nullptr && blockIdx.y == 0;
   uint4 hb[kAhead], wb[kAhead];
 #pragma unroll
