@@ -337,10 +337,10 @@ __global__ __launch_bounds__(64 * kChunkWaves) void chunk_place_kernel(
   // Wavefront w sums chunks w, w + 16, ...: all of them, and those before c0.
   // Bound by its chain of latencies (one round of loads, the scan, the
   // placement): the scan as four strided experts a lane, with its chunks'
-  // counts read from memory there, made it 8.7 us at 2048 tokens, now 6.4.
+  // counts read from memory there, made it 7.3 us at 2048 tokens, now 5.5.
   // 16 loads in flight: 16 chunks of the one block of up to 64 experts, or
   // four chunks of each of the four blocks.  With the blocks one after the
-  // other here and in the scan, 256 experts and 32 chunks took 10.1 us; now 5.1.
+  // other here and in the scan, 256 experts and 33 chunks took 12.1 us; now 4.7.
   auto sum_chunks = [&](auto blocks_c) __attribute__((always_inline)) {
     constexpr int kQ = decltype(blocks_c)::value;
     constexpr int kBatch = 16 / kQ;
